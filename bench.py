@@ -95,8 +95,11 @@ def kernel_source_hash():
     comment edit leaves the committed counters valid; a code change does not)."""
     import re
     h = hashlib.sha256()
-    for name in ("lb_kernels.hip", "lb_device.hpp"):
-        with open(os.path.join(ROOT, "paper_1004_5058_amd", "csrc", name), encoding="utf-8") as f:
+    for name in ("lb_kernels.hip", "lb_unit.hip", "lb_step.hpp", "lb_device.hpp"):
+        path = os.path.join(ROOT, "paper_1004_5058_amd", "csrc", name)
+        if not os.path.exists(path):
+            continue
+        with open(path, encoding="utf-8") as f:
             src = f.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
         src = re.sub(r"//[^\n]*", " ", src)

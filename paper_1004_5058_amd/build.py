@@ -17,7 +17,7 @@ LIB = os.path.join(LIBDIR, "liblbmi.so")
 
 # lb_host.cpp is host-only C++ (parameter validation, the tuning-cache format,
 # checkpoint header checks), compiled here and, separately, by the sanitizer test.
-SOURCES = ["lb_kernels.hip", "lb_capi.hip", "mlp_kernels.hip", "lb_host.cpp"]
+SOURCES = ["lb_kernels.hip", "lb_unit.hip", "lb_capi.hip", "mlp_kernels.hip", "lb_host.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

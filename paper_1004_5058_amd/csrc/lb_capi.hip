@@ -71,6 +71,12 @@ using lbh::storage_size;
 // Bytes per site of FP64 staging a state buffer must hold (four arrays).
 constexpr size_t STAGE_BYTES_PER_SITE = 4 * sizeof(double);
 
+// Population buffers above this size (both together) are stored non-temporally by
+// the single-step kernels: the GPU's last-level cache holds 256 MiB, and what
+// fits stays there for the next step (1024 x 512 FP32, 151 MB: 18.2 against 25.5
+// us per step with non-temporal stores; 4096^2, 2.4 GB: 0.476 against 0.468 ms).
+constexpr size_t STREAM_BYTES = (size_t)256 << 20;
+
 // Values stored per site: 18 populations, or the 6 moments of the tau = 1 form.
 size_t planes_of(int storage) { return storage >= LB_MOM32 ? 6 : 18; }
 // Storages with a fused two-steps-per-pass kernel: FP32 and the 16-bit forms.
@@ -89,6 +95,15 @@ lb_status validate(const lb_params* p, int storage0)
     return LB_OK;
 }
 
+// tau is 1 in the storage's arithmetic type: the collision replaces every
+// population by its equilibrium, and the lattice runs the kernels of lb_unit.hip.
+bool unit_tau(const lb_params& p)
+{
+    // (BF16: the general kernels, whose roundings its results follow)
+    if (p.storage == LB_BF16DEV) return false;
+    return p.storage == LB_F64 ? p.tau == 1.0 : (float)p.tau == 1.0f && (float)(1.0 / p.tau) == 1.0f;
+}
+
 struct Lat {
     lb_params p;
     int pitch = 0, ngroups = 0, ngroups2 = 0;   // profile partial rows: single-step, fused
@@ -96,6 +111,13 @@ struct Lat {
     size_t off_f[2] = {0, 0}, off_stress = 0, off_prof = 0, off_body = 0, end = 0;
     double rho_ref[2] = {0, 0};
 };
+
+// Strips of a lattice as wide as one wave of its narrowest step kernel stores.
+int wave_strips(const lb_params& p)
+{
+    const int w = is_mom(p.storage) ? lbk::MOM_COLS : lbk::UNIT_COLS;
+    return (p.nx + w - 1) / w;
+}
 
 // FP64 entries of a lattice's profile accumulators (when enabled).
 size_t prof_entries(const Lat& a) { return (size_t)(a.ngroups + a.ngroups2) * (size_t)a.p.ny; }
@@ -116,18 +138,17 @@ Layout plan(std::vector<Lat>& lats)
     L.off_part = align_up(sizeof(lbk::LatDesc) * n, ALIGN);
     L.off_res = L.off_part + align_up(sizeof(double) * 5 * lbk::sums_blocks(), ALIGN);
     // results: 5 sums + flag slot + 2 per lattice stress + profile staging handled in f buffers
-    // Item -> lattice table: at most ceil(nx/60) * ny items per lattice (the
-    // narrowest tile collides 60 columns: 64 lanes of the moment form, whose
-    // tiles overlap by four; one row per segment) plus 7 alignment slots each.
+    // Item -> lattice table: at most one item per row and narrowest tile (one
+    // wave: UNIT_COLS columns, MOM_COLS in the moment form).
     long long items = 0;
-    for (const auto& a : lats) items += (long long)((a.p.nx + 59) / 60) * a.p.ny + 7;
+    for (const auto& a : lats) items += (long long)wave_strips(a.p) * a.p.ny;
     L.max_items = (int)std::min<long long>(items, INT32_MAX);
     // Fused two-step tiles: strips of at least the narrowest width's output
     // columns, at most one row per segment.
     long long items2 = 0;
     for (const auto& a : lats) {
         const int tw = lbk::fuse2_tw(a.p.storage, lbk::FUSE2_NW_MIN);
-        items2 += (long long)((a.p.nx + tw - 1) / tw) * a.p.ny + 7;
+        items2 += (long long)((a.p.nx + tw - 1) / tw) * a.p.ny;
     }
     L.max_items2 = (int)std::min<long long>(items2, INT32_MAX);
     L.off_tiles = L.off_res + align_up(sizeof(double) * (8 + 2 * n), ALIGN);
@@ -137,9 +158,10 @@ Layout plan(std::vector<Lat>& lats)
         const size_t es = storage_size(a.p.storage);
         a.pitch = (int)lbh::row_pitch(a.p.nx);
         a.plane = (long long)lbh::plane_stride(a.p.nx, a.p.ny);
-        // profile accumulator rows: one per 64 columns, or for the moment form
-        // one per tile of the narrowest launch shape (60 collided columns)
-        a.ngroups = is_mom(a.p.storage) ? (a.p.nx + 59) / 60 : (a.p.nx + 63) / 64;
+        // profile accumulator rows: one per strip of one wave, or per 64 columns
+        // where the fused kernel's rows follow (the strips of one wave then run on
+        // into those: they are never more than both together)
+        a.ngroups = fusion_storage(a.p.storage) ? (a.p.nx + 63) / 64 : wave_strips(a.p);
         // and, for the storages with a fused two-step kernel, its partials:
         // two steps x strips x waves per step, for the widest of its layouts
         a.ngroups2 = 0;
@@ -181,6 +203,7 @@ void fill_desc(const Lat& a, lbk::LatDesc& d)
     d.ny = p.ny;
     d.pitch = a.pitch;
     d.walls = p.walls_y;
+    d.unit = is_mom(p.storage) || unit_tau(p);
     d.ngroups = a.ngroups;
     d.ngroups2 = a.ngroups2;
     d.tau = p.tau;
@@ -191,7 +214,10 @@ void fill_desc(const Lat& a, lbk::LatDesc& d)
     for (int s = 0; s < 2; ++s) {
         d.ks[s][0] = ga[s] * W1[0] + gr[s] * P12[0];
         d.ks[s][1] = ga[s] * W1[1] + gr[s] * P12[1];
-        for (int k = 2; k < 5; ++k) d.ks[s][k] = gr[s] * P12[k];
+        for (int k = 2; k < 5; ++k) {
+            d.ks[s][k] = gr[s] * P12[k];
+            d.kd[s][k - 2] = 2.0 * d.ks[s][k];
+        }
     }
     d.kx[0] = p.g_ab / p.rho0 * W1[0];
     d.kx[1] = p.g_ab / p.rho0 * W1[1];
@@ -211,11 +237,17 @@ void fill_desc(const Lat& a, lbk::LatDesc& d)
     d.frho0 = (float)d.rho0;
     d.finv_rho0 = (float)d.inv_rho0;
     for (int s = 0; s < 2; ++s)
+    {
         for (int k = 0; k < 5; ++k) d.fks[s][k] = (float)d.ks[s][k];
+        for (int k = 0; k < 3; ++k) d.fkd[s][k] = (float)d.kd[s][k];
+    }
     d.fkx[0] = (float)d.kx[0];
     d.fkx[1] = (float)d.kx[1];
     d.fu_top = (float)d.u_top;
     d.fu_bot = (float)d.u_bot;
+    d.fshift = std::exp2((float)std::lround(std::log2(a.p.rho0 / 13)));
+    d.flu_top = (float)(d.u_top - (double)d.fu_top);
+    d.flu_bot = (float)(d.u_bot - (double)d.fu_bot);
 }
 
 }  // namespace
@@ -230,6 +262,8 @@ struct lbb_handle {
     std::vector<lbk::LatDesc> descs;
     Layout lay;
     int storage = 1;
+    bool stream_stores = false;      // the lattices' buffers exceed the caches
+    bool any_unit = false, any_general = false;   // lattices of either kind (unit_tau)
     char* base = nullptr;
     size_t bytes = 0;
     hipStream_t stream = nullptr;
@@ -295,29 +329,50 @@ std::vector<int> fused_order(const lbb_handle* h, int ly2)
     return ord;
 }
 
-// Makespan, in ticks, of the fused tiles of height at most ly2 (each lattice's
-// rows split into fused_nseg near-equal segments, as the kernel does), handed
-// out in fused_order and scheduled greedily on `slots` concurrent blocks; a
-// tile of h rows costs h + 8 ticks (the overlap rows of the two steps).
-long long fused_makespan(const lbb_handle* h, int ly2, int slots)
+// Makespan, in ticks, of tiles of `columns` x at most `rows` (fused: each lattice's
+// rows split into fused_nseg near-equal segments and handed out tallest first, as
+// the kernels do), scheduled greedily on `slots` concurrent blocks; a tile of h rows
+// costs h + extra ticks.  The blocks go to the eight XCDs in turn (xcd_tile): the
+// first takes the most tiles, and its schedule is the answer.
+long long makespan(const lbb_handle* h, bool fused, int columns, int rows, int slots, int extra)
 {
     std::priority_queue<long long, std::vector<long long>, std::greater<long long>> free_at;
-    for (int c = 0; c < slots; ++c) free_at.push(0);
+    for (int c = 0; c < std::max(1, slots / 8); ++c) free_at.push(0);
     long long end = 0;
-    const int tw = lbk::fuse2_tw(h->storage, h->fnw_eff);
-    for (int k : fused_order(h, ly2)) {
+    int rot = 0;
+    for (int k : fused_order(h, fused ? rows : INT32_MAX)) {
         const Lat& a = h->lats[k];
-        const int strips = (a.p.nx + tw - 1) / tw;
-        const int nseg = lbh::fused_nseg(a.p.ny, ly2), sb = a.p.ny / nseg, sx = a.p.ny - sb * nseg;
-        for (int st = 0; st < strips; ++st)
-            for (int g = 0; g < nseg; ++g) {
-                const long long t = free_at.top() + sb + (g < sx ? 1 : 0) + 8;
-                free_at.pop();
-                free_at.push(t);
-                end = std::max(end, t);
-            }
+        const int strips = (a.p.nx + columns - 1) / columns;
+        const int nseg = fused ? lbh::fused_nseg(a.p.ny, rows) : (a.p.ny + rows - 1) / rows;
+        const int height = fused ? (a.p.ny + nseg - 1) / nseg : std::min(rows, a.p.ny);
+        const long long n = (long long)strips * nseg;
+        for (long long i = n / 8 + (((8 - rot) & 7) < n % 8 ? 1 : 0); i > 0; --i) {
+            const long long t = free_at.top() + height + extra;
+            free_at.pop();
+            free_at.push(t);
+            end = std::max(end, t);
+        }
+        rot = (int)((rot + n) % 8);
     }
     return end;
+}
+
+// The same for the fused tiles: the overlap rows of the two steps take 8 ticks, at
+// tau = 1 (whose halves stage one row per tick from the first) 12.
+long long fused_makespan(const lbb_handle* h, int ly2, int slots)
+{
+    return makespan(h, true, lbk::fuse2_tw(h->storage, h->fnw_eff), ly2, slots, h->any_general ? 8 : 12);
+}
+
+// How many fused blocks of nw waves of output columns the device runs on one
+// compute unit (a batch of both kinds runs two launches per pass; the fewer
+// blocks count).
+int fused_blocks_per_cu(const lbb_handle* h, int nw)
+{
+    int n = INT32_MAX;
+    if (h->any_unit) n = std::min(n, lbk::step2_unit_blocks_per_cu(h->storage, nw));
+    if (h->any_general) n = std::min(n, lbk::step2_blocks_per_cu(h->storage, nw));
+    return n;
 }
 
 int device_cus()
@@ -347,7 +402,7 @@ const int FUSED_HEIGHTS[] = {20, 28, 36, 44, 52, 60, 68, 76, 84, 92, 100, 108, 1
 int auto_ly2(const lbb_handle* h)
 {
     int maxny = 1;
-    const int slots = device_cus() * std::max(1, lbk::step2_blocks_per_cu(h->storage, h->fnw_eff));
+    const int slots = device_cus() * std::max(1, fused_blocks_per_cu(h, h->fnw_eff));
     const int tw = lbk::fuse2_tw(h->storage, h->fnw_eff);
     for (const Lat& a : h->lats) maxny = std::max(maxny, a.p.ny);
     int best = maxny;
@@ -373,6 +428,21 @@ int auto_fnw(const lbb_handle* h)
 {
     int best = 2, best_w = -1;
     if (!fusion_storage(h->storage)) return best;
+    if (!h->any_general) {
+        // tau = 1: the least strips x rows, weighted by what a row of a strip of each
+        // width costs (4096^2: FP32 0.317, 0.263 and 0.271 ms per step at 128, 192 and
+        // 256 lanes, FP16 0.175, 0.239 and 0.192, times the strip's columns)
+        static const int cost[2][5] = {{0, 0, 39, 48, 67}, {0, 0, 21, 44, 47}};
+        const int* c = cost[h->storage == LB_F32 ? 0 : 1];
+        long long best_t = -1;
+        for (int nw : {2, 3, 4}) {
+            const int tw = lbk::fuse2_tw(h->storage, nw);
+            long long t = 0;
+            for (const Lat& a : h->lats) t += (long long)((a.p.nx + tw - 1) / tw) * a.p.ny * c[nw];
+            if (best_t < 0 || t < best_t) { best_t = t; best = nw; }
+        }
+        return best;
+    }
     for (int nw : {2, 4}) {
         const int w = lbk::step2_blocks_per_cu(h->storage, nw) * 2 * nw;
         if (w >= best_w) { best_w = w; best = nw; }
@@ -380,9 +450,8 @@ int auto_fnw(const lbb_handle* h)
     return best;
 }
 
-// Work decomposition for launch shape (bx, ly): tiles per lattice, each
-// lattice's first item rounded up to a multiple of 8 (one tile per XCD slot),
-// and the item -> lattice table the step kernel reads (-1: padding).
+// Work decomposition for launch shape (bx, ly): tiles per lattice, and the
+// item -> lattice table the step kernel reads.
 lb_status decompose(lbb_handle* h)
 {
     int item = 0;
@@ -391,17 +460,17 @@ lb_status decompose(lbb_handle* h)
     for (size_t k = 0; k < h->lats.size(); ++k) {
         const Lat& a = h->lats[k];
         lbk::LatDesc& d = h->descs[k];
-        // the moment form's tiles overlap by four columns: bx - 4 collided per tile
-        const int wt = is_mom(h->storage) ? h->bx - 4 : h->bx;
+        // columns of a tile: bx, but for waves that work on their own (the moment form,
+        // 64-column tiles at tau = 1)
+        const int wt = is_mom(h->storage) ? h->bx / 64 * lbk::MOM_COLS
+                                          : (d.unit && h->bx == 64 ? lbk::UNIT_COLS : h->bx);
         d.nstrip = (a.p.nx + wt - 1) / wt;
         d.ly = std::min(std::min(h->ly, a.p.ny), 256);   // the kernel's halo buffer holds 256 rows
         d.nseg = (a.p.ny + d.ly - 1) / d.ly;
         h->ly_max = std::max(h->ly_max, d.ly);
         d.nitems = d.nstrip * d.nseg;
-        item = (item + 7) / 8 * 8;
         d.item_begin = item;
-        item += (d.nitems + 7) / 8 * 8;   // padding items keep the XCD-banded order (xcd_tile)
-        h->tiles.resize(d.item_begin, -1);
+        item += d.nitems;
         h->tiles.resize(item, (int32_t)k);
     }
     if (item > h->lay.max_items) return fail(LB_EINVAL, "launch shape gives more work items than planned");
@@ -424,10 +493,8 @@ lb_status decompose(lbb_handle* h)
         d.nseg2 = lbh::fused_nseg(a.p.ny, ly2);
         d.ly2 = (a.p.ny + d.nseg2 - 1) / d.nseg2;   // the tallest segment
         d.nitems2 = d.nstrip2 * d.nseg2;
-        item2 = (item2 + 7) / 8 * 8;
         d.item_begin2 = item2;
-        item2 += (d.nitems2 + 7) / 8 * 8;
-        h->tiles2.resize(d.item_begin2, -1);
+        item2 += d.nitems2;
         h->tiles2.resize(item2, (int32_t)k);
     }
     if (item2 > h->lay.max_items2) return fail(LB_EINVAL, "fused tile height gives more work items than planned");
@@ -451,8 +518,18 @@ int launch_grid(const lbb_handle* h)
 
 lb_status launch_one(lbb_handle* h, hipStream_t s, int src, int first = 0)
 {
-    hipError_t e = lbk::launch_step(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(),
-                                    h->ntot, src, first, launch_grid(h), h->ly_max, s);
+    hipError_t e = hipSuccess;
+    if (is_mom(h->storage)) {
+        e = lbk::launch_step_mom(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(), h->ntot, src, first,
+                                 launch_grid(h), s);
+    } else {
+        if (h->any_unit)
+            e = lbk::launch_step_unit(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(), h->ntot, src,
+                                      h->stream_stores, launch_grid(h), s);
+        if (e == hipSuccess && h->any_general)
+            e = lbk::launch_step(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(), h->ntot, src,
+                                 h->stream_stores, launch_grid(h), h->ly_max, s);
+    }
     if (e != hipSuccess) return fail(LB_EDEVICE, "step launch failed: %s", hipGetErrorString(e));
     return LB_OK;
 }
@@ -460,8 +537,12 @@ lb_status launch_one(lbb_handle* h, hipStream_t s, int src, int first = 0)
 // Steps t and t+1 in one launch: reads buffer src, writes buffer src ^ 1.
 lb_status launch_two(lbb_handle* h, hipStream_t s, int src)
 {
-    hipError_t e = lbk::launch_step2(h->storage, h->fnw_eff, h->base, h->d_desc(), h->d_tiles2(), h->ntot2, src,
-                                     std::max(1, h->ntot2), s);
+    const int grid = std::max(1, h->ntot2);
+    hipError_t e = hipSuccess;
+    if (h->any_unit)
+        e = lbk::launch_step2_unit(h->storage, h->fnw_eff, h->base, h->d_desc(), h->d_tiles2(), h->ntot2, src, grid, s);
+    if (e == hipSuccess && h->any_general)
+        e = lbk::launch_step2(h->storage, h->fnw_eff, h->base, h->d_desc(), h->d_tiles2(), h->ntot2, src, grid, s);
     if (e != hipSuccess) return fail(LB_EDEVICE, "fused step launch failed: %s", hipGetErrorString(e));
     return LB_OK;
 }
@@ -646,7 +727,13 @@ lb_status batch_init(const lb_params* params, int32_t n, void* dev_state, size_t
     h->bytes = bytes;
     h->stream = (hipStream_t)stream;
     h->descs.resize(n);
-    for (int k = 0; k < n; ++k) fill_desc(lats[k], h->descs[k]);
+    size_t fbytes = 0;
+    for (const Lat& a : lats) fbytes += 2 * planes_of(h->storage) * (size_t)a.plane * storage_size(h->storage);
+    h->stream_stores = fbytes > STREAM_BYTES;
+    for (int k = 0; k < n; ++k) {
+        fill_desc(lats[k], h->descs[k]);
+        (h->descs[k].unit ? h->any_unit : h->any_general) = true;
+    }
     default_shape(h);
     lb_status st = decompose(h);
     if (st != LB_OK) { delete h; return st; }
@@ -769,29 +856,59 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
     return LB_OK;
 }
 
-// Default launch shape: the widest tile and tallest row segment that still
-// give about sixteen work items per compute unit.  A block marches its segment
-// row by row and each row waits on memory, so small lattices and small
-// batches split into a few tall items leave the chip idle; big lattices keep
-// wide, tall items (fewer segment prologues and halo columns).
+// Default launch shape.  A block marches its segment row by row and each row
+// waits on memory, so small lattices and small batches split into a few tall
+// items leave the chip idle; big lattices keep wide, tall items (fewer segment
+// prologues and halo columns).
+//
+// tau = 1 and moment form, lattices that stay in the caches: one-wave tiles, as
+// tall as still gives a wave per SIMD (the moment form, whose rows are a third of
+// the bytes: two).  us per step by rows per tile, the chosen one starred: 256 x 128
+// FP32 6.8* (1) 7.5 (2) 9.0 (4); 512 x 256 FP32 10.2 (1) 9.4* (2) 10.3 (4); 512^2 FP32
+// 12.8 (2) 12.4* (4) 15.1 (8).  Larger ones: 512-column tiles (256 in FP64), one per
+// compute unit: 4096^2 FP32 0.457 ms (512 x 128) against 0.468 (256 x 64), FP16 0.254
+// against 0.367; the height whose tiles, handed out in
+// rounds, finish first.
+//
+// Otherwise: the widest tile and tallest segment that still give about sixteen
+// items per compute unit.
 void default_shape(lbb_handle* h)
 {
-    int dev = 0, ncu = 256;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-        ncu = prop.multiProcessorCount;
+    const long long ncu = device_cus();
     int maxnx = 0;
     for (const Lat& a : h->lats) maxnx = std::max(maxnx, a.p.nx);
+    auto items = [&](int columns, int rows) {
+        long long n = 0;
+        for (const Lat& a : h->lats)
+            n += (long long)((a.p.nx + columns - 1) / columns) * ((a.p.ny + rows - 1) / rows);
+        return n;
+    };
+    if (!h->any_general) {
+        const bool mom = is_mom(h->storage);
+        if (mom || !h->stream_stores) {
+            h->bx = 64;
+            for (int ly : {16, 8, 4, 2, 1}) {
+                h->ly = ly;
+                if (items(mom ? lbk::MOM_COLS : lbk::UNIT_COLS, ly) >= (mom ? 8 : 4) * ncu) return;
+            }
+            return;
+        }
+        h->bx = h->storage == LB_F64 ? 256 : 512;
+        long long best = -1;
+        for (int ly = 128; ly >= 16; ly -= 4) {
+            // one block per compute unit at a time; a row costs a tick, a tile six more
+            const long long t = makespan(h, false, h->bx, ly, (int)ncu, 6);
+            if (best < 0 || t < best) { best = t; h->ly = ly; }
+        }
+        return;
+    }
     const int bxmax = maxnx >= 256 ? 256 : (maxnx >= 128 ? 128 : 64);
     static const int cand[][2] = {{256, 64}, {256, 32}, {256, 16}, {128, 16}, {64, 16}, {64, 8}};
     for (const auto& c : cand) {
         if (c[0] > bxmax) continue;
-        long long items = 0;
-        for (const Lat& a : h->lats)
-            items += (long long)((a.p.nx + c[0] - 1) / c[0]) * ((a.p.ny + c[1] - 1) / c[1]);
         h->bx = c[0];
         h->ly = c[1];
-        if (items >= 16ll * ncu) return;
+        if (items(c[0], c[1]) >= 16 * ncu) return;
     }
 }
 
@@ -820,6 +937,7 @@ int device_lds_limit()
 }
 bool shape_fits(const lbb_handle* h, int bx, int ly)
 {
+    if (!h->any_general) return true;   // the tau = 1 and moment kernels use no LDS
     const size_t need = shape_lds(h, bx, ly);
     return need > 0 && need <= (size_t)device_lds_limit();
 }
@@ -855,7 +973,8 @@ lb_status check_fused_lds(const lbb_handle* h, int nw)
     int dev = 0, lim = 65536;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    const size_t need = lbk::step2_lds_bytes(h->storage, nw);
+    const size_t need = std::max(h->any_general ? lbk::step2_lds_bytes(h->storage, nw) : 0,
+                                 h->any_unit ? lbk::step2_unit_lds_bytes(h->storage, nw) : 0);
     if (need == 0 || need > (size_t)lim)
         return fail(LB_EINVAL, "two steps per pass with %d lanes per step need %zu bytes of LDS per block, the device "
                     "allows %d", 64 * nw, need, lim);
@@ -1090,7 +1209,7 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     if (st == LB_OK && best1.bx && fusion_allowed(h)) {
         for (int lanes : {128, 192, 256}) {
             if (st != LB_OK) break;
-            if (lbk::step2_blocks_per_cu(h->storage, lanes / 64) < 1) continue;
+            if (fused_blocks_per_cu(h, lanes / 64) < 1) continue;
             std::vector<int> heights = {0};
             for (int c : FUSED_HEIGHTS)
                 if (c <= 300) heights.push_back(c);
@@ -1413,9 +1532,19 @@ lb_status lb_load(lb_handle* h, const void* buf, size_t bytes)
     CHECK_H(h);
     lbb_handle* b = &h->b;
     const Lat& a = b->lats[0];
-    lbh::CkptHeader hd;
+    lbh::CkptHeader hd, want = ckpt_header_of(b);
+    // FP64 and moment-form checkpoints whose profile has a row per 64 and 60
+    // columns (as these forms kept it before their strips followed the waves)
+    // fill the first rows; the sums over the rows are what is read.
+    const uint64_t all = want.pbytes;
+    if (buf && bytes >= sizeof hd && !fusion_storage(b->storage) && a.p.profile) {
+        std::memcpy(&hd, buf, sizeof hd);
+        const int w = is_mom(b->storage) ? 60 : 64;
+        const uint64_t fewer = (uint64_t)((a.p.nx + w - 1) / w) * (uint64_t)a.p.ny * sizeof(double);
+        if (hd.pbytes == fewer) want.pbytes = fewer;
+    }
     std::string msg;
-    const lb_status st = lbh::check_checkpoint(buf, bytes, ckpt_header_of(b), &hd, &msg);
+    const lb_status st = lbh::check_checkpoint(buf, bytes, want, &hd, &msg);
     if (st != LB_OK) return fail(st, "%s", msg.c_str());
     const char* p = (const char*)buf;
     b->cur = 0;
@@ -1425,6 +1554,8 @@ lb_status lb_load(lb_handle* h, const void* buf, size_t bytes)
     if (hd.pbytes)
         HIP_TRY(hipMemcpyAsync(b->base + a.off_prof, p + sizeof hd + hd.fbytes + hd.sbytes, hd.pbytes,
                                hipMemcpyHostToDevice, b->stream));
+    HIP_TRY(lbk::launch_fill((double*)(b->base + a.off_prof + hd.pbytes), (long long)((all - hd.pbytes) / sizeof(double)),
+                             0.0, b->stream));
     HIP_TRY(hipStreamSynchronize(b->stream));
     b->t = hd.t;
     b->nsamples = hd.nsamples;

@@ -17,7 +17,8 @@ struct LatDesc {
     long long off_body;    // [ny] FP64: external body force F_x(y) of each row; < 0: none
     long long plane;       // elements per (species, direction) plane = ny * pitch
     int nx, ny, pitch, walls;
-    int item_begin;        // first global work item of this lattice (multiple of 8)
+    int unit;              // tau is 1 in the arithmetic type: the step is lb_unit.hip's
+    int item_begin;        // first global work item of this lattice
     int nitems;            // nstrip * nseg
     int nstrip, nseg, ly;  // tiles: strips of bx columns, segments of ly rows
     int ngroups;           // ceil(nx / 64) (moment form: ceil(nx / 60))
@@ -30,6 +31,7 @@ struct LatDesc {
     int item_begin2, nitems2, nstrip2, nseg2, ly2;
     double tau, omega, rho0, inv_rho0;
     double ks[2][5];       // psi-stencil coefficient of species s on the shells |c|^2 = 1,2,4,5,8
+    double kd[2][3];       // twice the coefficients on the shells 4, 5, 8 (offsets two rows or columns away)
     double kx[2];          // cross coefficient (G_AB/rho0) w on |c|^2 = 1, 2
     double u_top, u_bot;
     double wref[18];       // storage base w_i rho_ref_s, index s*9 + i (populations are stored
@@ -40,8 +42,11 @@ struct LatDesc {
     // The same coefficients rounded to FP32, for the FP32-arithmetic kernels.
     float ftau, fomega, frho0, finv_rho0;
     float fks[2][5];
+    float fkd[2][3];
     float fkx[2];
     float fu_top, fu_bot;
+    float fshift;             // a power of two near rho_0 / 13, a species' sum of three populations (lb_unit.hip)
+    float flu_top, flu_bot;   // what FP32 leaves of u_top, u_bot
     float frref[2], fpsiref[2], fepsi[2];
 };
 

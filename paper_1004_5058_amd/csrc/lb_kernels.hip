@@ -20,380 +20,11 @@
 // The three population rows in flight live in registers, so every
 // population is read once and written once per step; the only re-reads are
 // the halo columns and the two halo rows at each end of a segment.
-#include "lb_device.hpp"
-#include "lb_kernels.hpp"
-#include <type_traits>
+
+#include "lb_step.hpp"
 
 namespace lbk {
 
-// ---------------------------------------------------------------- storage --
-
-// Every format stores the deviation d_is = f_is - w_i rho_ref_s of a population
-// from the rest equilibrium at the lattice's reference densities; arithmetic
-// is FP64 for FP64 storage and FP32 otherwise.  fast_psi: the pseudo-potential
-// from the hardware 2^x instead of expm1 (see dpsi).
-struct StF64 { using S = double;   using C = double; static constexpr bool fast_psi = false; };
-struct StF32 { using S = float;    using C = float;  static constexpr bool fast_psi = false; };
-struct StF16 { using S = _Float16; using C = float;  static constexpr bool fast_psi = true; };
-struct StBF16 { using S = __bf16;  using C = float;  static constexpr bool fast_psi = true; };
-
-template <class C> struct V4;
-template <> struct V4<float> { using T = float4; };
-template <> struct V4<double> { using T = double4; };
-
-// Raw buffer access.  A block addresses each species' plane stack through a
-// buffer resource: the per-lane column byte offset is the VGPR offset and the
-// uniform (direction, row) byte offset is the SGPR offset, so the 18 loads and
-// 18 stores of a row need no 64-bit address arithmetic.
-using rsrc_t = __amdgpu_buffer_rsrc_t;
-constexpr int RSRC_WORD3 = 0x00020000;
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void* p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, RSRC_WORD3);
-}
-
-template <class S> __device__ __forceinline__ S bload(rsrc_t r, unsigned voff, unsigned soff);
-template <> __device__ __forceinline__ float bload<float>(rsrc_t r, unsigned voff, unsigned soff)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, (int)soff, 0));
-}
-template <> __device__ __forceinline__ double bload<double>(rsrc_t r, unsigned voff, unsigned soff)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(double, (u2)__builtin_amdgcn_raw_buffer_load_b64(r, voff, (int)soff, 0));
-}
-template <> __device__ __forceinline__ _Float16 bload<_Float16>(rsrc_t r, unsigned voff, unsigned soff)
-{
-    return __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, voff, (int)soff, 0));
-}
-template <> __device__ __forceinline__ __bf16 bload<__bf16>(rsrc_t r, unsigned voff, unsigned soff)
-{
-    return __builtin_bit_cast(__bf16, __builtin_amdgcn_raw_buffer_load_b16(r, voff, (int)soff, 0));
-}
-
-// Buffer store of one value; CP is the instruction's cache policy (0: default,
-// CP_NT: non-temporal).
-constexpr int CP_NT = 2;
-template <class S, int CP = 0> __device__ __forceinline__ void bstore(S v, rsrc_t r, unsigned voff, unsigned soff)
-{
-    if constexpr (std::is_same<S, float>::value) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, (int)soff, CP);
-    } else if constexpr (std::is_same<S, double>::value) {
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, voff, (int)soff, CP);
-    } else {
-        static_assert(sizeof(S) == 2, "2-, 4- and 8-byte values");
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, voff, (int)soff, CP);
-    }
-}
-
-// Load / store one deviation, converting between the storage and the
-// arithmetic type (round to nearest even on the way down).  The SGPR offset is
-// uniform by construction; readfirstlane states it, so a store under a
-// divergent branch does not become a per-lane loop.
-template <class P>
-__device__ __forceinline__ typename P::C ld(rsrc_t r, unsigned voff, unsigned soff)
-{
-    return (typename P::C)bload<typename P::S>(r, voff, __builtin_amdgcn_readfirstlane(soff));
-}
-
-template <class P>
-__device__ __forceinline__ void st(rsrc_t r, unsigned voff, unsigned soff, typename P::C v)
-{
-    bstore<typename P::S>((typename P::S)v, r, voff, (unsigned)__builtin_amdgcn_readfirstlane((int)soff));
-}
-template <class P, int CP = 0>
-__device__ __forceinline__ void st_s(rsrc_t r, unsigned voff, unsigned soff, typename P::S v)
-{
-    bstore<typename P::S, CP>(v, r, voff, (unsigned)__builtin_amdgcn_readfirstlane((int)soff));
-}
-
-// A value of the arithmetic type, rounded to the storage format on its own:
-// the value is first rounded to the arithmetic type, so the compiler cannot
-// fuse the conversion into the multiply-add that produced it (for FP16 that
-// fusion, v_fma_mixlo_f16, rounds once and can differ in the last bit; which
-// stores it fuses would otherwise depend on the code around them).
-template <class S, class C>
-__device__ __forceinline__ S to_store(C x)
-{
-    if constexpr (std::is_same<S, C>::value) {
-        return x;
-    } else {
-        asm("" : "+v"(x));
-        return (S)x;
-    }
-}
-
-// Two values of the arithmetic type rounded to the storage format on their own
-// (FP16 as to_store, BF16 as the plain conversion).  16-bit storage from FP32:
-// one packed conversion, which rounds each half as the single conversion does.
-template <class S, class C>
-__device__ __forceinline__ void to_store2(C a, C b, S& sa, S& sb)
-{
-    if constexpr (sizeof(S) == 2 && std::is_same<C, float>::value) {
-        typedef float f2 __attribute__((ext_vector_type(2)));
-        typedef S s2 __attribute__((ext_vector_type(2)));
-        if constexpr (std::is_same<S, _Float16>::value) {
-            asm("" : "+v"(a));
-            asm("" : "+v"(b));
-        }
-        const s2 h = __builtin_convertvector((f2){a, b}, s2);
-        sa = h.x;
-        sb = h.y;
-    } else {
-        sa = to_store<S>(a);
-        sb = to_store<S>(b);
-    }
-}
-
-// The 18 populations of one site held in registers between the row load and
-// the collision: the arithmetic type for 32/64-bit storage; for 16-bit storage
-// the raw values, two per VGPR (d16 loads fill the low and high halves), and
-// converted when read.  Besides single values a row gives the sums the
-// collision needs, in one fixed order (left to right): the species densities
-// (dens), the momentum (mom), the deviation f_q - x of one population from a
-// value (dev), and the post-collision value f_q - w t in the storage format,
-// rounded from its FP32 value (post).
-template <class P, bool PACK = (sizeof(typename P::S) == 2)> struct Row;
-
-// The sums in the arithmetic type, through the row's operator[].
-template <class R, class C>
-__device__ __forceinline__ void row_dens(const R& f, C& da, C& db)
-{
-    da = f[0];
-    db = f[9];
-#pragma unroll
-    for (int q = 1; q < 9; ++q) { da += f[q]; db += f[9 + q]; }
-}
-template <class R, class C>
-__device__ __forceinline__ void row_mom(const R& f, C& jx, C& jy)
-{
-    jx = (f[1] - f[3] + f[5] - f[6] - f[7] + f[8]) + (f[10] - f[12] + f[14] - f[15] - f[16] + f[17]);
-    jy = (f[2] - f[4] + f[5] + f[6] - f[7] - f[8]) + (f[11] - f[13] + f[14] + f[15] - f[16] - f[17]);
-}
-
-// FP16 halves enter FP32 sums through the mixed-precision multiply-add
-// v_fma_mix_f32 (an operand may be the low or high FP16 half of a VGPR): the
-// widening is exact and a*1 + c rounds once, so each step equals the FP32 add
-// of the converted value bit for bit, without the conversion instruction.
-// mix_acc: x + s h, mix_pair: a + s b, mix_dev: h - x (s = +1 or -1; h, a, b
-// the halves H, HA, HB of the packed pairs).
-template <int H, bool NEG>
-__device__ __forceinline__ float mix_acc(unsigned p, float x)
-{
-    float r;
-    if constexpr (NEG && H)
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
-    else if constexpr (NEG)
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
-    else if constexpr (H)
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
-    else
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
-    return r;
-}
-template <int HA, int HB, bool NEG>
-__device__ __forceinline__ float mix_pair(unsigned a, unsigned b)
-{
-    float r;
-    if constexpr (NEG)
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[%c3,0,%c4] op_sel_hi:[1,0,1]"
-            : "=v"(r) : "v"(b), "v"(a), "n"(HB), "n"(HA));
-    else
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[%c3,0,%c4] op_sel_hi:[1,0,1]"
-            : "=v"(r) : "v"(b), "v"(a), "n"(HB), "n"(HA));
-    return r;
-}
-template <int H>
-__device__ __forceinline__ float mix_dev(unsigned p, float x)
-{
-    float r;
-    if constexpr (H)
-        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
-    else
-        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
-    return r;
-}
-
-template <class P> struct Row<P, false> {
-    using C = typename P::C;
-    C v[18];
-    __device__ __forceinline__ C operator[](int q) const { return v[q]; }
-    __device__ __forceinline__ void dens(C& da, C& db) const { row_dens(*this, da, db); }
-    __device__ __forceinline__ void mom(C& jx, C& jy) const { row_mom(*this, jx, jy); }
-    __device__ __forceinline__ C dev(int q, C x) const { return v[q] - x; }
-    __device__ __forceinline__ C post(int q, C w, C t) const { return v[q] - w * t; }   // S = C
-    // Planes are stored shifted in x by c_ix: population q of the lane's node
-    // sits one column left (c_ix = +1: vl), in place (vc) or one column right
-    // (c_ix = -1: vr).  so: uniform SGPR byte offset; v*: per-lane byte offsets.
-    __device__ __forceinline__ void load(rsrc_t r0, rsrc_t r1, unsigned vl, unsigned vc, unsigned vr, unsigned so,
-                                         unsigned pbytes)
-    {
-#pragma unroll
-        for (int q = 0; q < 18; ++q) {
-            const int cx = CX[q % 9];
-            v[q] = ld<P>(q < 9 ? r0 : r1, cx > 0 ? vl : (cx < 0 ? vr : vc), so + (q % 9) * pbytes);
-        }
-    }
-};
-
-template <class P> struct Row<P, true> {
-    using S = typename P::S;
-    typedef S S2 __attribute__((ext_vector_type(2)));
-    S2 v[9];
-    static constexpr bool MIX = std::is_same<S, _Float16>::value;
-    __device__ __forceinline__ float operator[](int q) const
-    {
-        return (float)((q & 1) ? v[q >> 1].y : v[q >> 1].x);
-    }
-    template <int Q> __device__ __forceinline__ unsigned u() const { return __builtin_bit_cast(unsigned, v[Q >> 1]); }
-    template <int Q, bool NEG> __device__ __forceinline__ float acc(float x) const
-    {
-        return mix_acc<Q & 1, NEG>(u<Q>(), x);
-    }
-    template <int QA, int QB, bool NEG> __device__ __forceinline__ float pair() const
-    {
-        return mix_pair<QA & 1, QB & 1, NEG>(u<QA>(), u<QB>());
-    }
-    __device__ __forceinline__ void dens(float& da, float& db) const
-    {
-        if constexpr (MIX) {
-            da = acc<8, false>(acc<7, false>(acc<6, false>(acc<5, false>(
-                acc<4, false>(acc<3, false>(acc<2, false>(pair<0, 1, false>())))))));
-            db = acc<17, false>(acc<16, false>(acc<15, false>(acc<14, false>(
-                acc<13, false>(acc<12, false>(acc<11, false>(pair<9, 10, false>())))))));
-        } else {
-            row_dens(*this, da, db);
-        }
-    }
-    __device__ __forceinline__ void mom(float& jx, float& jy) const
-    {
-        if constexpr (MIX) {
-            const float ax = acc<8, false>(acc<7, true>(acc<6, true>(acc<5, false>(pair<1, 3, true>()))));
-            const float bx = acc<17, false>(acc<16, true>(acc<15, true>(acc<14, false>(pair<10, 12, true>()))));
-            const float ay = acc<8, true>(acc<7, true>(acc<6, false>(acc<5, false>(pair<2, 4, true>()))));
-            const float by = acc<17, true>(acc<16, true>(acc<15, false>(acc<14, false>(pair<11, 13, true>()))));
-            jx = ax + bx;
-            jy = ay + by;
-        } else {
-            row_mom(*this, jx, jy);
-        }
-    }
-    __device__ __forceinline__ float dev(int q, float x) const
-    {
-        if constexpr (MIX) {
-            const unsigned p = __builtin_bit_cast(unsigned, v[q >> 1]);
-            return (q & 1) ? mix_dev<1>(p, x) : mix_dev<0>(p, x);
-        } else {
-            return (*this)[q] - x;
-        }
-    }
-    // the FP32 value rounded to the storage format (FP16 through to_store:
-    // the compiler would otherwise fuse the conversion into the multiply-add
-    // at some stores and not at others; BF16 has no such fusion)
-    __device__ __forceinline__ S post(int q, float w, float t) const
-    {
-        if constexpr (MIX) return to_store<S>((*this)[q] - w * t);
-        else return (S)((*this)[q] - w * t);
-    }
-    __device__ __forceinline__ void load(rsrc_t r0, rsrc_t r1, unsigned vl, unsigned vc, unsigned vr, unsigned so,
-                                         unsigned pbytes)
-    {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int q0 = 2 * k, q1 = 2 * k + 1;
-            const int c0 = CX[q0 % 9], c1 = CX[q1 % 9];
-            v[k].x = bload<S>(q0 < 9 ? r0 : r1, c0 > 0 ? vl : (c0 < 0 ? vr : vc),
-                              (unsigned)__builtin_amdgcn_readfirstlane((int)(so + (q0 % 9) * pbytes)));
-            v[k].y = bload<S>(q1 < 9 ? r0 : r1, c1 > 0 ? vl : (c1 < 0 ? vr : vc),
-                              (unsigned)__builtin_amdgcn_readfirstlane((int)(so + (q1 % 9) * pbytes)));
-        }
-    }
-};
-
-// Deviation of the pseudo-potential from its value at the reference density:
-// psi(rho_ref + d) - psi(rho_ref) = -E expm1(-d/rho0), E = rho0 exp(-rho_ref/rho0).
-__device__ __forceinline__ float dpsi_of(float d, float e, float inv_rho0)
-{
-    return -e * expm1f(-d * inv_rho0);
-}
-__device__ __forceinline__ double dpsi_of(double d, double e, double inv_rho0)
-{
-    return -e * expm1(-d * inv_rho0);
-}
-// The same deviation as E (1 - 2^(-d log2(e) / rho0)) with the hardware
-// base-2 exponential (one transcendental and two multiply-adds instead of the
-// ~24 instructions of expm1f).  Its absolute error is a few 1e-8 of E: far
-// below the storage rounding of the 16-bit forms, about one FP32 rounding of
-// the populations per step in the FP32 moment form.  The forms whose step is
-// bound by arithmetic use it (fast_psi); FP32 and FP64 population storage
-// keep expm1.
-template <class P>
-__device__ __forceinline__ typename P::C dpsi(typename P::C d, typename P::C e, typename P::C inv_rho0)
-{
-    if constexpr (P::fast_psi) {
-        const float t = __builtin_amdgcn_exp2f(d * (-1.4426950408889634f * inv_rho0));
-        return e - e * t;
-    } else {
-        return dpsi_of(d, e, inv_rho0);
-    }
-}
-
-// Reciprocal: the hardware approximation (<= 1 ulp) in FP32, exact division in FP64.
-__device__ __forceinline__ float rcp(float v) { return __builtin_amdgcn_rcpf(v); }
-__device__ __forceinline__ double rcp(double v) { return 1.0 / v; }
-
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// A 32-bit lane move by DPP control CTRL applied to both halves of an FP64
-// value (all 64 lanes active).
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x)
-{
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
-    const unsigned lo = __builtin_amdgcn_update_dpp(0u, (unsigned)b, CTRL, 0xF, 0xF, false);
-    const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
-// The wave-wide sums of two vectors at once (FP64, all 64 lanes active),
-// without the LDS crossbar: the sum of d0 ends in lanes 0..31, of d1 in lanes
-// 32..63.  The gfx950 row swap v_permlane32_swap exchanges the upper half of
-// d0 with the lower half of d1, so one addition does the lane-distance-32
-// step of both; v_permlane16_swap then pairs 16-lane rows; the rest is the
-// xor butterfly over lane distances 1 and 2 (DPP quad permutations), then 4
-// and 8 (the half-row and row mirrors: after the first steps every lane of a
-// quad, then of an 8-lane group, holds the same value, so the mirror's
-// partner holds what the xor partner holds).  About half the work of two
-// separate wave sums.
-__device__ __forceinline__ double wave_sum2_dpp(double d0, double d1)
-{
-    auto lo = [](double x) { return (unsigned)__builtin_bit_cast(unsigned long long, x); };
-    auto hi = [](double x) { return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32); };
-    auto mk = [](unsigned l, unsigned h) { return __builtin_bit_cast(double, ((unsigned long long)h << 32) | l); };
-    // first result: d0's lower half, then d1's lower half moved up; second:
-    // d0's upper half moved down, then d1's upper half
-    const auto l32 = __builtin_amdgcn_permlane32_swap(lo(d0), lo(d1), false, false);
-    const auto h32 = __builtin_amdgcn_permlane32_swap(hi(d0), hi(d1), false, false);
-    double v = mk(l32[0], h32[0]) + mk(l32[1], h32[1]);
-    // with both operands v: the first result holds, in odd rows, the even row
-    // below; the second, in even rows, the odd row above
-    const auto l16 = __builtin_amdgcn_permlane16_swap(lo(v), lo(v), false, false);
-    const auto h16 = __builtin_amdgcn_permlane16_swap(hi(v), hi(v), false, false);
-    const bool odd = (__lane_id() >> 4) & 1;
-    v += odd ? mk(l16[0], h16[0]) : mk(l16[1], h16[1]);
-    v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]: lane l^1
-    v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]: lane l^2
-    v += dpp_move<0x141>(v);   // row_half_mirror: the other quad of the 8-lane group
-    v += dpp_move<0x140>(v);   // row_mirror: the other 8-lane group of the 16-lane row
-    return v;
-}
 
 // Force stencil sums of one site.  P(dy, dx) and R(dy, dx) return the staged
 // (species A, species B) psi and rho deviations of the neighbour at offset
@@ -483,54 +114,6 @@ __device__ __forceinline__ void stencil_sums(FP P, FR R, const C* ks0, const C* 
     s[4] = cxA; s[5] = cyA; s[6] = cxB; s[7] = cyB;
 }
 
-// Work item l of a lattice with n tiles -> its tile, or -1 for a padding item.
-// Each lattice's items start at a multiple of 8 and fill a multiple of 8
-// slots, and blocks go to the eight XCDs in turn (block b to XCD b mod 8), so
-// XCD x runs items x, x + 8, x + 16, ...: they map to the contiguous tiles
-// x c .. x c + c - 1 (c = ceil(n / 8), tiles numbered strip-fastest), so
-// neighbouring tiles, which share halo rows and columns, share an XCD's L2.
-__device__ __forceinline__ int xcd_tile(int l, int n)
-{
-    const int c = (n + 7) >> 3;
-    if (l >= 8 * c) return -1;
-    const int lin = (l & 7) * c + (l >> 3);
-    return lin < n ? lin : -1;
-}
-
-template <class P>
-__device__ __forceinline__ int map_row(int r, int ny, int walls)
-{
-    if (walls) {
-        if (r < 0) r = -1 - r;
-        else if (r >= ny) r = 2 * ny - 1 - r;
-    } else {
-        r %= ny;
-        if (r < 0) r += ny;
-    }
-    return r;
-}
-
-// ------------------------------------------------------------------ step ---
-
-template <class C> struct V2;
-template <> struct V2<float> { using T = float2; };
-template <> struct V2<double> { using T = double2; };
-
-// Workgroup barrier that orders LDS only: this wave's LDS reads and writes
-// complete (lgkmcnt 0), then s_barrier.  Global loads issued before it stay in
-// flight (the row prefetch), and so do direct-to-LDS halo loads: only the wave
-// that issued those reads their data, behind its own vmcnt wait.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // gfx9 encoding: lgkmcnt(0), vmcnt/expcnt unchanged
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-// Largest segment (rows per tile).
-constexpr int LY_MAX = 256;
-
 // Dynamic LDS of the step kernel: the four halo columns of a segment
 // (rows y0-2 .. y1+1), staged only by the formats without the direct-to-LDS
 // halo (4-byte storage always has it), and the per-wave row sums of u_x for
@@ -546,7 +129,7 @@ __host__ __device__ constexpr size_t step_dyn_lds(int bx, int ly)
     return step_halo_lds<P>(ly) + sizeof(double) * (size_t)(bx / 64) * ly;
 }
 
-template <int BX, class P>
+template <int BX, class P, int CP>
 __global__ void __launch_bounds__(BX)
 k_step(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
        int src)
@@ -583,11 +166,10 @@ k_step(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __
     auto halo_wave = [&](int r) { return r & (HW - 1); };
 
     for (int w = blockIdx.x; w < ntot; w += gridDim.x) {
-        const int L = tiles[w];          // owning lattice, -1 for alignment padding
-        if (L < 0) continue;
+        const int L = tiles[w];          // owning lattice
         const LatDesc& d = descs[L];
+        if (d.unit) continue;            // tau = 1: lb_unit.hip
         const int lin = xcd_tile(w - d.item_begin, d.nitems);
-        if (lin < 0) continue;
         const int nstrip = d.nstrip;
         const int strip = lin % nstrip, seg = lin / nstrip;
         const int nx = d.nx, ny = d.ny, pitch = d.pitch, walls = d.walls;
@@ -841,16 +423,16 @@ k_step(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __
                 for (int i = 0; i < 9; ++i) ps[i] = f.post(o + i, omega, t[i]);
                 auto fs = [&](int i) -> C { return f[o + i] - omega * t[i]; };
                 const rsrc_t ro = (s == 0) ? rout0 : rout1;
-                // non-temporal stores: the launch never reads what it writes
-                // (1.3-2 % faster per step at 4096^2; the two-step kernel's
-                // stores ran slower with this policy)
+                // CP: non-temporal where the lattices exceed the caches (1.3-2 %
+                // faster per step at 4096^2; the two-step kernel's stores ran
+                // slower with this policy)
                 if (!(bot || top)) {
                     // interior row: push to rows y-1, y, y+1 (periodic wrap)
 #pragma unroll
                     for (int i = 0; i < 9; ++i) {
                         const int cy = CY[i];
                         const unsigned vrow = (cy < 0) ? vrow_m : (cy > 0 ? vrow_p : vrow_0);
-                        st_s<P, CP_NT>(ro, vrow + vc, i * pbytes, ps[i]);
+                        st_s<P, CP>(ro, vrow + vc, i * pbytes, ps[i]);
                     }
                     return;
                 }
@@ -864,15 +446,15 @@ k_step(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __
                         const C uw = (cy < 0) ? u_bot : u_top;
                         if (cx != 0) {
                             const C back = fs(i) - (C)(1.0 / 6.0) * rs * (C)cx * uw;
-                            st_s<P, CP_NT>(ro, vrow_0 + vback, OPP[i] * pbytes, to_store<S>(back));
+                            st_s<P, CP>(ro, vrow_0 + vback, OPP[i] * pbytes, to_store<S>(back));
                             if (cy < 0) mom_b += (C)cx * (fs(i) + back);
                             else mom_t += (C)cx * (fs(i) + back);
                         } else {
-                            st_s<P, CP_NT>(ro, vrow_0 + vback, OPP[i] * pbytes, ps[i]);
+                            st_s<P, CP>(ro, vrow_0 + vback, OPP[i] * pbytes, ps[i]);
                         }
                     } else {
                         const unsigned vrow = (cy < 0) ? vrow_m : (cy > 0 ? vrow_p : vrow_0);
-                        st_s<P, CP_NT>(ro, vrow + vc, i * pbytes, ps[i]);
+                        st_s<P, CP>(ro, vrow + vc, i * pbytes, ps[i]);
                     }
                 }
             };
@@ -1039,11 +621,10 @@ k_step2(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* _
     }
 
     for (int w = blockIdx.x; w < ntot; w += gridDim.x) {
-        const int L = tiles[w];
-        if (L < 0) continue;
+        const int L = tiles[w];          // owning lattice
         const LatDesc& d = descs[L];
+        if (d.unit) continue;
         const int lin = xcd_tile(w - d.item_begin2, d.nitems2);
-        if (lin < 0) continue;
         const int nstrip = d.nstrip2;
         const int strip = lin % nstrip, seg = lin / nstrip;
         const int nx = d.nx, ny = d.ny, pitch = d.pitch, walls = d.walls;
@@ -1739,327 +1320,6 @@ k_copy(const float4* __restrict__ src, float4* __restrict__ dst, long long n)
 // holds the initial state itself, (rho_s - rho_ref_s, u, u), and the first
 // step reads it in place: the initial populations are local equilibria, not
 // streamed ones.
-struct MomF32 { using S = float;  using C = float;  static constexpr bool fast_psi = true; };
-struct MomF64 { using S = double; using C = double; static constexpr bool fast_psi = false; };
-
-// Deviation of the equilibrium population i of one species from w_i rho_ref:
-// w_i [drho + rho (3 c.u + 4.5 (c.u)^2 - 1.5 u.u)], rho = rho_ref + drho.
-template <int I, class C>
-__device__ __forceinline__ C eq_dev(C drho, C rho, C vx, C vy)
-{
-    constexpr double W = (I == 0) ? 4.0 / 9.0 : (I < 5 ? 1.0 / 9.0 : 1.0 / 36.0);
-    const C cu = (C)CX[I] * vx + (C)CY[I] * vy;
-    const C usq = vx * vx + vy * vy;
-    return (C)W * (drho + rho * ((C)3 * cu + (C)4.5 * cu * cu - (C)1.5 * usq));
-}
-
-template <class C>
-__host__ __device__ constexpr size_t mom_dyn_lds(int bx, int ly)
-{
-    return sizeof(double) * (size_t)(bx / 64) * ly;
-}
-
-template <int BX, class P>
-__global__ void __launch_bounds__(BX)
-k_step_mom(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
-           int src, int first)
-{
-    using S = typename P::S;
-    using C = typename P::C;
-    using C2 = typename V2<C>::T;
-    // Overlapped tiles: the BX lanes hold columns x0-2 .. x0+BX-3 and every
-    // lane rebuilds its own column, so the psi/rho neighbourhood of the BX-4
-    // columns x0 .. x0+BX-5 that the tile collides needs no extra halo work.
-    // Moment rows in flight: four rows of the pairs (drho, v_x, v_y) of A and B
-    // for columns x0-3 .. x0+BX-2 (index column - x0 + 3); psi and rho pairs of
-    // the six rows around the collided one for the lanes' columns (index tid).
-    __shared__ C2 mring[4][3][BX + 2];
-    __shared__ C2 ringP[6][BX];
-    __shared__ C2 ringR[6][BX];
-    extern __shared__ __align__(16) char dyn_lds[];
-
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6;
-
-    for (int w = blockIdx.x; w < ntot; w += gridDim.x) {
-        const int L = tiles[w];
-        if (L < 0) continue;
-        const LatDesc& d = descs[L];
-        const int lin = xcd_tile(w - d.item_begin, d.nitems);
-        if (lin < 0) continue;
-        const int nstrip = d.nstrip;
-        const int strip = lin % nstrip, seg = lin / nstrip;
-        const int nx = d.nx, ny = d.ny, pitch = d.pitch, walls = d.walls;
-        const long long plane = d.plane;
-        const int x0 = strip * (BX - 4);
-        const int y0 = seg * d.ly;
-        const int y1 = min(y0 + d.ly, ny);
-        auto wrap = [&](int c) { c %= nx; return c < 0 ? c + nx : c; };
-        const int x = x0 - 2 + tid;                       // the lane's column
-        const bool valid = tid >= 2 && tid < BX - 2 && x < nx;   // collided by this tile
-        const unsigned xc = (unsigned)wrap(x);
-
-        const C inv_rho0 = coef<C>(d.inv_rho0, d.finv_rho0);
-        C ks0[5], ks1[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            ks0[k] = coef<C>(d.ks[0][k], d.fks[0][k]);
-            ks1[k] = coef<C>(d.ks[1][k], d.fks[1][k]);
-        }
-        const C kx1 = coef<C>(d.kx[0], d.fkx[0]), kx2 = coef<C>(d.kx[1], d.fkx[1]);
-        const C u_top = coef<C>(d.u_top, d.fu_top), u_bot = coef<C>(d.u_bot, d.fu_bot);
-        const C rref0 = coef<C>(d.rref[0], d.frref[0]), rref1 = coef<C>(d.rref[1], d.frref[1]);
-        const C pref0 = coef<C>(d.psiref[0], d.fpsiref[0]), pref1 = coef<C>(d.psiref[1], d.fpsiref[1]);
-        const C e0 = coef<C>(d.epsi[0], d.fepsi[0]), e1 = coef<C>(d.epsi[1], d.fepsi[1]);
-
-        const int es = (int)sizeof(S);
-        const unsigned mbytes = (unsigned)(6 * plane * (long long)es);
-        const rsrc_t rin = make_rsrc(base + d.off_f[src], mbytes);
-        const rsrc_t rout = make_rsrc(base + d.off_f[src ^ 1], mbytes);
-        const unsigned pbytes = (unsigned)(plane * es), rbytes = (unsigned)(pitch * es);
-        const unsigned vc = xc * es;
-        const int cm = tid + 1;                           // the lane's moment-ring index
-        // lanes 0 and 1 also load the two outer moment columns x0-3 and
-        // x0+BX-2 (ring indices 0 and BX+1)
-        const int hm = (tid == 0) ? 0 : BX + 1;
-        const unsigned vhm = (unsigned)wrap(x0 - 3 + hm) * es;
-        double* __restrict__ stress = (double*)(base + d.off_stress);
-        double* __restrict__ prof = d.off_prof >= 0 ? (double*)(base + d.off_prof) : nullptr;
-        const double* __restrict__ body = d.off_body >= 0 ? (const double*)(base + d.off_body) : nullptr;
-        double* profS = (double*)dyn_lds;                   // [BX/64][ly] per-wave row sums
-        C mom_b = 0, mom_t = 0;
-
-        // One moment row in registers: the lane's column and, for lanes 0 and
-        // 1, an outer column.  Rows beyond a wall do not exist and are skipped.
-        struct MR { C v[6]; C h[6]; };
-        auto mrow_ok = [&](int r) { return !walls || (r >= 0 && r < ny); };
-        auto mload = [&](MR& m, int r) {
-            if (!mrow_ok(r)) return;
-            const unsigned so = (unsigned)map_row<P>(r, ny, walls) * rbytes;
-#pragma unroll
-            for (int p = 0; p < 6; ++p) m.v[p] = ld<P>(rin, vc, so + p * pbytes);
-            if (tid < 2) {
-#pragma unroll
-                for (int p = 0; p < 6; ++p) m.h[p] = ld<P>(rin, vhm, so + p * pbytes);
-            }
-        };
-        auto mput = [&](const MR& m, int r) {
-            if (!mrow_ok(r)) return;
-            const int sl = r & 3;
-            mring[sl][0][cm] = C2{m.v[0], m.v[1]};
-            mring[sl][1][cm] = C2{m.v[2], m.v[3]};
-            mring[sl][2][cm] = C2{m.v[4], m.v[5]};
-            if (tid < 2) {
-                mring[sl][0][hm] = C2{m.h[0], m.h[1]};
-                mring[sl][1][hm] = C2{m.h[2], m.h[3]};
-                mring[sl][2][hm] = C2{m.h[4], m.h[5]};
-            }
-        };
-
-        // Incoming populations of row r (a fluid row) at the lane's column,
-        // summed into the density deviations of A and B and the momentum j.
-        auto pull = [&](int r, C& dA, C& dB, C& jx, C& jy) {
-            if (first) {
-                const int sl = r & 3;
-                const C2 m0 = mring[sl][0][cm], m1 = mring[sl][1][cm], m2 = mring[sl][2][cm];
-                dA = m0.x;
-                dB = m0.y;
-                const C ra = rref0 + dA, rb = rref1 + dB;
-                jx = ra * m1.x + rb * m1.y;
-                jy = ra * m2.x + rb * m2.y;
-                return;
-            }
-            const bool bot = walls && r == 0, top = walls && r == ny - 1;
-            dA = dB = jx = jy = 0;
-            auto one = [&](auto I) {
-                constexpr int i = decltype(I)::value;
-                constexpr int cx = CX[i], cy = CY[i];
-                C fa, fb;
-                if ((cy > 0 && bot) || (cy < 0 && top)) {
-                    // source beyond the wall: the site's own population OPP[i],
-                    // returned with the moving-wall term (1/6) rho_s c_ix u_w
-                    constexpr int o = OPP[i];
-                    const int sl = r & 3;
-                    const C2 m0 = mring[sl][0][cm], m1 = mring[sl][1][cm], m2 = mring[sl][2][cm];
-                    const C ra = rref0 + m0.x, rb = rref1 + m0.y;
-                    const C uw = (cy > 0) ? u_bot : u_top;
-                    fa = eq_dev<o>(m0.x, ra, m1.x, m2.x);
-                    fb = eq_dev<o>(m0.y, rb, m1.y, m2.y);
-                    if (cx != 0) {
-                        fa += (C)(1.0 / 6.0) * ra * (C)cx * uw;
-                        fb += (C)(1.0 / 6.0) * rb * (C)cx * uw;
-                    }
-                } else {
-                    const int sl = (r - cy) & 3;
-                    const int cs = cm - cx;
-                    const C2 m0 = mring[sl][0][cs], m1 = mring[sl][1][cs], m2 = mring[sl][2][cs];
-                    fa = eq_dev<i>(m0.x, rref0 + m0.x, m1.x, m2.x);
-                    fb = eq_dev<i>(m0.y, rref1 + m0.y, m1.y, m2.y);
-                }
-                dA += fa;
-                dB += fb;
-                if (cx != 0) jx += (C)cx * (fa + fb);
-                if (cy != 0) jy += (C)cy * (fa + fb);
-                // keep each direction's LDS reads next to their arithmetic (bounds
-                // the registers the pull occupies: three waves per SIMD)
-                asm volatile("" : "+v"(dA), "+v"(dB), "+v"(jx), "+v"(jy)::"memory");
-            };
-            one(std::integral_constant<int, 0>{});
-            one(std::integral_constant<int, 1>{});
-            one(std::integral_constant<int, 2>{});
-            one(std::integral_constant<int, 3>{});
-            one(std::integral_constant<int, 4>{});
-            one(std::integral_constant<int, 5>{});
-            one(std::integral_constant<int, 6>{});
-            one(std::integral_constant<int, 7>{});
-            one(std::integral_constant<int, 8>{});
-        };
-
-        auto slot6 = [&](int r) { return __builtin_amdgcn_readfirstlane((r - y0 + 2) % 6); };
-        // Stage row r: (psi, rho) deviations of the lane's column into the
-        // rings and its momentum into J.  A row beyond a wall is the even
-        // mirror of the fluid rows.
-        auto stage = [&](int r, C2& J) {
-            const int sl = slot6(r);
-            if (walls && (r < 0 || r >= ny)) {
-                const int sm = slot6((r < 0) ? -1 - r : 2 * ny - 1 - r);
-                ringP[sl][tid] = ringP[sm][tid];
-                ringR[sl][tid] = ringR[sm][tid];
-                return;
-            }
-            C dA, dB, jx, jy;
-            pull(r, dA, dB, jx, jy);
-            ringP[sl][tid] = C2{dpsi<P>(dA, e0, inv_rho0), dpsi<P>(dB, e1, inv_rho0)};
-            ringR[sl][tid] = C2{dA, dB};
-            J = C2{jx, jy};
-        };
-
-        // Collide row y: the force from the 5x5 neighbourhood, the shifted
-        // velocities (tau = 1) and the six new moments of the site.
-        auto collide = [&](int y, const C2& J) {
-            int sl[5];
-            sl[0] = __builtin_amdgcn_readfirstlane((y - y0) % 6);
-#pragma unroll
-            for (int k = 1; k < 5; ++k) sl[k] = (sl[k - 1] == 5) ? 0 : sl[k - 1] + 1;
-            // neighbour columns clamped to the tile: the edge lanes read in
-            // range and are not collided
-            auto cn = [&](int dx) { return min(max(tid + dx, 0), BX - 1); };
-            C ss[8];
-            stencil_sums<true, C>([&](int dy, int dx) { return ringP[sl[dy + 2]][cn(dx)]; },
-                            [&](int dy, int dx) { return ringR[sl[dy + 2]][cn(dx)]; }, ks0, ks1, kx1, kx2, ss);
-            const C sxA = ss[0], syA = ss[1], sxB = ss[2], syB = ss[3];
-            const C cxA = ss[4], cyA = ss[5], cxB = ss[6], cyB = ss[7];
-            const C2 p0 = ringP[sl[2]][tid];
-            const C2 r0c = ringR[sl[2]][tid];
-            const C ra = rref0 + r0c.x, rb = rref1 + r0c.y;
-            const C pa = pref0 + p0.x, pb = pref1 + p0.y;
-            const C FxA = -pa * sxA - ra * cxA, FyA = -pa * syA - ra * cyA;
-            const C FxB = -pb * sxB - rb * cxB, FyB = -pb * syB - rb * cyB;
-            const C inv_rho = rcp(ra + rb);
-            const C ux = J.x * inv_rho, uy = J.y * inv_rho;
-            const C gx = (body != nullptr) ? (C)body[y] * inv_rho : (C)0;
-            if (prof != nullptr) {
-                double su = valid ? (double)ux : 0.0;
-                su = wave_sum(su);
-                if ((tid & 63) == 0) profS[wave * d.ly + (y - y0)] = su;
-            }
-            const C iA = rcp(ra), iB = rcp(rb);
-            const C vAx = ux + (FxA * iA + gx), vAy = uy + FyA * iA;
-            const C vBx = ux + (FxB * iB + gx), vBy = uy + FyB * iB;
-            if (!valid) return;
-            const unsigned so = (unsigned)y * rbytes;
-            st<P>(rout, vc, so, r0c.x);
-            st<P>(rout, vc, so + pbytes, r0c.y);
-            st<P>(rout, vc, so + 2 * pbytes, vAx);
-            st<P>(rout, vc, so + 3 * pbytes, vBx);
-            st<P>(rout, vc, so + 4 * pbytes, vAy);
-            st<P>(rout, vc, so + 5 * pbytes, vBy);
-            // wall momentum of the links that leave through a wall this step:
-            // c_ix (f*_i + back), back = f*_i - (1/6) rho_s c_ix u_w
-            if (walls && (y == 0 || y == ny - 1)) {
-                auto link = [&](auto I, C uw, C& acc) {
-                    constexpr int i = decltype(I)::value;
-                    constexpr int cx = CX[i];
-                    const C fa = (C)(i < 5 ? 1.0 / 9.0 : 1.0 / 36.0) * ra + eq_dev<i>((C)0, ra, vAx, vAy);
-                    const C fb = (C)(i < 5 ? 1.0 / 9.0 : 1.0 / 36.0) * rb + eq_dev<i>((C)0, rb, vBx, vBy);
-                    const C ba = fa - (C)(1.0 / 6.0) * ra * (C)cx * uw;
-                    const C bb = fb - (C)(1.0 / 6.0) * rb * (C)cx * uw;
-                    acc += (C)cx * (fa + ba) + (C)cx * (fb + bb);
-                };
-                if (y == 0) {
-                    link(std::integral_constant<int, 7>{}, u_bot, mom_b);
-                    link(std::integral_constant<int, 8>{}, u_bot, mom_b);
-                }
-                if (y == ny - 1) {
-                    link(std::integral_constant<int, 5>{}, u_top, mom_t);
-                    link(std::integral_constant<int, 6>{}, u_top, mom_t);
-                }
-            }
-        };
-
-        // Prologue: moment rows y0-3 .. y0+3 through the ring, psi/rho rows
-        // y0-2 .. y0+1 staged (fluid rows first, then the mirrored ghost rows),
-        // row y0+4 prefetched.  Loop: entering iteration y, moment rows
-        // y+1 .. y+3 are in LDS, row y+4 in registers, and psi/rho rows
-        // y-2 .. y+1 staged.
-        C2 J0 = C2{0, 0}, J1 = C2{0, 0}, J2 = C2{0, 0}, J3 = C2{0, 0}, Jx = C2{0, 0};
-        {
-            MR a, b, c, e;
-            mload(a, y0 - 3);
-            mload(b, y0 - 2);
-            mload(c, y0 - 1);
-            mload(e, y0);
-            mput(a, y0 - 3);
-            mput(b, y0 - 2);
-            mput(c, y0 - 1);
-            mput(e, y0);
-            lds_barrier();
-            if (mrow_ok(y0 - 2)) stage(y0 - 2, Jx);
-            if (mrow_ok(y0 - 1)) stage(y0 - 1, Jx);
-            lds_barrier();
-            mload(a, y0 + 1);
-            mload(b, y0 + 2);
-            mput(a, y0 + 1);
-            mput(b, y0 + 2);
-            lds_barrier();
-            if (mrow_ok(y0)) stage(y0, J0);
-            if (mrow_ok(y0 + 1)) stage(y0 + 1, J1);
-            for (int r = y0 - 2; r <= y0 + 1; ++r)
-                if (!mrow_ok(r)) stage(r, Jx);
-            lds_barrier();
-            mload(a, y0 + 3);
-            mput(a, y0 + 3);
-        }
-        MR pf;
-        if (y0 + 4 <= y1 + 2) mload(pf, y0 + 4);
-        lds_barrier();
-        auto iter = [&](int y, const C2& Jc, C2& Js) {
-            if (y + 4 <= y1 + 2) mput(pf, y + 4);
-            if (y + 5 <= y1 + 2) mload(pf, y + 5);
-            stage(y + 2, Js);
-            lds_barrier();
-            collide(y, Jc);
-        };
-        for (int y = y0; y < y1; y += 4) {
-            iter(y, J0, J2);
-            if (y + 1 < y1) iter(y + 1, J1, J3);
-            if (y + 2 < y1) iter(y + 2, J2, J0);
-            if (y + 3 < y1) iter(y + 3, J3, J1);
-        }
-        if (valid && walls && y0 == 0) stress[xc] += (double)mom_b;
-        if (valid && walls && y1 == ny) stress[nx + xc] += (double)mom_t;
-        __syncthreads();
-        if (prof != nullptr) {
-            // one accumulator row per tile: the per-wave sums in wave order
-            for (int r = tid; r < y1 - y0; r += BX) {
-                double t = 0;
-                for (int wv = 0; wv < BX / 64; ++wv) t += profS[wv * d.ly + r];
-                prof[(long long)strip * ny + y0 + r] += t;
-            }
-        }
-        __syncthreads();
-    }
-}
 
 // Population i of species s at site (x, y) in the moment form, FP64: the
 // equilibrium of its source site, across a wall the bounced population of the
@@ -2226,24 +1486,25 @@ k_line_profile_mom(char* __restrict__ base, const LatDesc* __restrict__ dd, int 
 // ---------------------------------------------------------- host launchers --
 
 template <int BX, class P>
-static hipError_t step_bx(char* base, const LatDesc* descs, const int* tiles, int ntot, int src, int grid,
+static hipError_t step_bx(char* base, const LatDesc* descs, const int* tiles, int ntot, int src, bool stream, int grid,
                           int ly, hipStream_t s)
 {
     const size_t dyn = step_dyn_lds<P>(BX, ly);
-    hipLaunchKernelGGL((k_step<BX, P>), dim3(grid), dim3(BX), dyn, s, base, descs, tiles, ntot, src);
+    if (stream) hipLaunchKernelGGL((k_step<BX, P, CP_NT>), dim3(grid), dim3(BX), dyn, s, base, descs, tiles, ntot, src);
+    else hipLaunchKernelGGL((k_step<BX, P, 0>), dim3(grid), dim3(BX), dyn, s, base, descs, tiles, ntot, src);
     return hipGetLastError();
 }
 
 template <class P>
-static hipError_t step_p(int bx, char* base, const LatDesc* descs, const int* tiles, int ntot, int src,
+static hipError_t step_p(int bx, char* base, const LatDesc* descs, const int* tiles, int ntot, int src, bool stream,
                          int grid, int ly, hipStream_t s)
 {
     switch (bx) {
-    case 64: return step_bx<64, P>(base, descs, tiles, ntot, src, grid, ly, s);
-    case 128: return step_bx<128, P>(base, descs, tiles, ntot, src, grid, ly, s);
-    case 256: return step_bx<256, P>(base, descs, tiles, ntot, src, grid, ly, s);
+    case 64: return step_bx<64, P>(base, descs, tiles, ntot, src, stream, grid, ly, s);
+    case 128: return step_bx<128, P>(base, descs, tiles, ntot, src, stream, grid, ly, s);
+    case 256: return step_bx<256, P>(base, descs, tiles, ntot, src, stream, grid, ly, s);
     case 512:   // 4- and 2-byte storage only: halves the share of halo columns
-        if constexpr (sizeof(typename P::S) <= 4) return step_bx<512, P>(base, descs, tiles, ntot, src, grid, ly, s);
+        if constexpr (sizeof(typename P::S) <= 4) return step_bx<512, P>(base, descs, tiles, ntot, src, stream, grid, ly, s);
         return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
@@ -2257,27 +1518,6 @@ static hipError_t step_p(int bx, char* base, const LatDesc* descs, const int* ti
     case 3: { using P = StBF16; return CALL; }                       \
     default: return hipErrorInvalidValue;                            \
     }
-
-template <int BX, class P>
-static hipError_t step_mom_bx(char* base, const LatDesc* descs, const int* tiles, int ntot, int src, int first,
-                              int grid, int ly, hipStream_t s)
-{
-    const size_t dyn = mom_dyn_lds<typename P::C>(BX, ly);
-    hipLaunchKernelGGL((k_step_mom<BX, P>), dim3(grid), dim3(BX), dyn, s, base, descs, tiles, ntot, src, first);
-    return hipGetLastError();
-}
-
-template <class P>
-static hipError_t step_mom_p(int bx, char* base, const LatDesc* descs, const int* tiles, int ntot, int src,
-                             int first, int grid, int ly, hipStream_t s)
-{
-    switch (bx) {
-    case 64: return step_mom_bx<64, P>(base, descs, tiles, ntot, src, first, grid, ly, s);
-    case 128: return step_mom_bx<128, P>(base, descs, tiles, ntot, src, first, grid, ly, s);
-    case 256: return step_mom_bx<256, P>(base, descs, tiles, ntot, src, first, grid, ly, s);
-    default: return hipErrorInvalidValue;
-    }
-}
 
 // Moment-form storage (tau = 1): codes 4 (FP32) and 5 (FP64).
 #define LBK_DISPATCH_MOM(storage, CALL)                              \
@@ -2299,27 +1539,21 @@ static size_t lds_of(K kernel, size_t dyn)
 size_t step_lds_bytes(int storage, int bx, int ly)
 {
     switch (storage * 1000 + bx) {
-    case 0 * 1000 + 64: return lds_of(k_step<64, StF64>, step_dyn_lds<StF64>(64, ly));
-    case 0 * 1000 + 128: return lds_of(k_step<128, StF64>, step_dyn_lds<StF64>(128, ly));
-    case 0 * 1000 + 256: return lds_of(k_step<256, StF64>, step_dyn_lds<StF64>(256, ly));
-    case 1 * 1000 + 64: return lds_of(k_step<64, StF32>, step_dyn_lds<StF32>(64, ly));
-    case 1 * 1000 + 128: return lds_of(k_step<128, StF32>, step_dyn_lds<StF32>(128, ly));
-    case 1 * 1000 + 256: return lds_of(k_step<256, StF32>, step_dyn_lds<StF32>(256, ly));
-    case 1 * 1000 + 512: return lds_of(k_step<512, StF32>, step_dyn_lds<StF32>(512, ly));
-    case 2 * 1000 + 64: return lds_of(k_step<64, StF16>, step_dyn_lds<StF16>(64, ly));
-    case 2 * 1000 + 128: return lds_of(k_step<128, StF16>, step_dyn_lds<StF16>(128, ly));
-    case 2 * 1000 + 256: return lds_of(k_step<256, StF16>, step_dyn_lds<StF16>(256, ly));
-    case 2 * 1000 + 512: return lds_of(k_step<512, StF16>, step_dyn_lds<StF16>(512, ly));
-    case 3 * 1000 + 64: return lds_of(k_step<64, StBF16>, step_dyn_lds<StBF16>(64, ly));
-    case 3 * 1000 + 128: return lds_of(k_step<128, StBF16>, step_dyn_lds<StBF16>(128, ly));
-    case 3 * 1000 + 256: return lds_of(k_step<256, StBF16>, step_dyn_lds<StBF16>(256, ly));
-    case 3 * 1000 + 512: return lds_of(k_step<512, StBF16>, step_dyn_lds<StBF16>(512, ly));
-    case 4 * 1000 + 64: return lds_of(k_step_mom<64, MomF32>, mom_dyn_lds<MomF32::C>(64, ly));
-    case 4 * 1000 + 128: return lds_of(k_step_mom<128, MomF32>, mom_dyn_lds<MomF32::C>(128, ly));
-    case 4 * 1000 + 256: return lds_of(k_step_mom<256, MomF32>, mom_dyn_lds<MomF32::C>(256, ly));
-    case 5 * 1000 + 64: return lds_of(k_step_mom<64, MomF64>, mom_dyn_lds<MomF64::C>(64, ly));
-    case 5 * 1000 + 128: return lds_of(k_step_mom<128, MomF64>, mom_dyn_lds<MomF64::C>(128, ly));
-    case 5 * 1000 + 256: return lds_of(k_step_mom<256, MomF64>, mom_dyn_lds<MomF64::C>(256, ly));
+    case 0 * 1000 + 64: return lds_of(k_step<64, StF64, 0>, step_dyn_lds<StF64>(64, ly));
+    case 0 * 1000 + 128: return lds_of(k_step<128, StF64, 0>, step_dyn_lds<StF64>(128, ly));
+    case 0 * 1000 + 256: return lds_of(k_step<256, StF64, 0>, step_dyn_lds<StF64>(256, ly));
+    case 1 * 1000 + 64: return lds_of(k_step<64, StF32, 0>, step_dyn_lds<StF32>(64, ly));
+    case 1 * 1000 + 128: return lds_of(k_step<128, StF32, 0>, step_dyn_lds<StF32>(128, ly));
+    case 1 * 1000 + 256: return lds_of(k_step<256, StF32, 0>, step_dyn_lds<StF32>(256, ly));
+    case 1 * 1000 + 512: return lds_of(k_step<512, StF32, 0>, step_dyn_lds<StF32>(512, ly));
+    case 2 * 1000 + 64: return lds_of(k_step<64, StF16, 0>, step_dyn_lds<StF16>(64, ly));
+    case 2 * 1000 + 128: return lds_of(k_step<128, StF16, 0>, step_dyn_lds<StF16>(128, ly));
+    case 2 * 1000 + 256: return lds_of(k_step<256, StF16, 0>, step_dyn_lds<StF16>(256, ly));
+    case 2 * 1000 + 512: return lds_of(k_step<512, StF16, 0>, step_dyn_lds<StF16>(512, ly));
+    case 3 * 1000 + 64: return lds_of(k_step<64, StBF16, 0>, step_dyn_lds<StBF16>(64, ly));
+    case 3 * 1000 + 128: return lds_of(k_step<128, StBF16, 0>, step_dyn_lds<StBF16>(128, ly));
+    case 3 * 1000 + 256: return lds_of(k_step<256, StBF16, 0>, step_dyn_lds<StBF16>(256, ly));
+    case 3 * 1000 + 512: return lds_of(k_step<512, StBF16, 0>, step_dyn_lds<StBF16>(512, ly));
     default: return 0;
     }
 }
@@ -2394,10 +1628,9 @@ int step2_blocks_per_cu(int storage, int nw)
 }
 
 hipError_t launch_step(int storage, int bx, char* base, const LatDesc* descs, const int* tiles, int ntot,
-                       int src, int first, int grid, int ly, hipStream_t s)
+                       int src, bool stream, int grid, int ly, hipStream_t s)
 {
-    LBK_DISPATCH_MOM(storage, (step_mom_p<P>(bx, base, descs, tiles, ntot, src, first, grid, ly, s)));
-    LBK_DISPATCH(storage, (step_p<P>(bx, base, descs, tiles, ntot, src, grid, ly, s)));
+    LBK_DISPATCH(storage, (step_p<P>(bx, base, descs, tiles, ntot, src, stream, grid, ly, s)));
 }
 
 static int grid_for(long long n, int threads)

@@ -7,11 +7,10 @@
 
 namespace lbk {
 
-// ly: the largest rows-per-tile of the lattices (sizes the dynamic LDS).
-// first: the step starts from the initial state (moment storage only: it then
-// reads the local equilibria in place instead of pulling from neighbours).
+// ly: the largest rows-per-tile of the lattices (sizes the dynamic LDS).  stream:
+// the lattices do not stay in the caches from step to step (non-temporal stores).
 hipError_t launch_step(int storage, int bx, char* base, const LatDesc* descs, const int* tiles, int ntot,
-                       int src, int first, int grid, int ly, hipStream_t s);
+                       int src, bool stream, int grid, int ly, hipStream_t s);
 // Steps t and t+1 in one launch (k_step2): reads buffer src, writes buffer
 // src ^ 1.  FP32 and 16-bit storage (codes 1, 2, 3); nw = 2, 3 or 4 waves per
 // step, blocks of 128 nw threads, tiles of fuse2_tw(storage, nw) output
@@ -21,6 +20,21 @@ hipError_t launch_step(int storage, int bx, char* base, const LatDesc* descs, co
 constexpr int fuse2_xo(int storage, int nw) { return (storage == 1 && nw == 2) ? 3 : 5; }
 constexpr int fuse2_tw(int storage, int nw) { return 64 * nw - 2 * fuse2_xo(storage, nw); }
 constexpr int FUSE2_NW_MIN = 2, FUSE2_NW_MAX = 4;
+// The same at tau = 1 (lb_unit.hip); each kernel steps only the lattices of its
+// kind (LatDesc::unit).  A wave of the single-step kernel stores UNIT_COLS
+// columns, one of the moment form MOM_COLS.
+constexpr int UNIT_COLS = 60, MOM_COLS = 58;
+hipError_t launch_step_unit(int storage, int bx, char* base, const LatDesc* descs, const int* tiles, int ntot, int src,
+                            bool stream, int grid, hipStream_t s);
+hipError_t launch_step_mom(int storage, int bx, char* base, const LatDesc* descs, const int* tiles, int ntot, int src,
+                           int first, int grid, hipStream_t s);
+hipError_t launch_step2_unit(int storage, int nw, char* base, const LatDesc* descs, const int* tiles, int ntot, int src,
+                             int grid, hipStream_t s);
+// (first: the step starts from the initial state: it reads the local equilibria
+// in place instead of pulling from neighbours.)
+// LDS bytes of one fused block, and the blocks the device keeps on one compute unit.
+size_t step2_unit_lds_bytes(int storage, int nw);
+int step2_unit_blocks_per_cu(int storage, int nw);
 hipError_t launch_step2(int storage, int nw, char* base, const LatDesc* descs, const int* tiles, int ntot, int src,
                         int grid, hipStream_t s);
 // LDS bytes of one fused block, and how many blocks the device keeps on one
