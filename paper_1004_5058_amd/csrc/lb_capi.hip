@@ -861,14 +861,19 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
 // items leave the chip idle; big lattices keep wide, tall items (fewer segment
 // prologues and halo columns).
 //
-// tau = 1 and moment form, lattices that stay in the caches: one-wave tiles, as
-// tall as still gives a wave per SIMD (the moment form, whose rows are a third of
-// the bytes: two).  us per step by rows per tile, the chosen one starred: 256 x 128
-// FP32 6.8* (1) 7.5 (2) 9.0 (4); 512 x 256 FP32 10.2 (1) 9.4* (2) 10.3 (4); 512^2 FP32
-// 12.8 (2) 12.4* (4) 15.1 (8).  Larger ones: 512-column tiles (256 in FP64), one per
-// compute unit: 4096^2 FP32 0.457 ms (512 x 128) against 0.468 (256 x 64), FP16 0.254
-// against 0.367; the height whose tiles, handed out in
-// rounds, finish first.
+// tau = 1 and moment form, lattices that stay in the caches: one-wave tiles of the
+// height that models fastest: a tile of ly rows takes ly + 3 row times, up to three
+// (moment form; 16-bit and FP32: two, FP64: one) waves of a SIMD share it, each further one
+// adding 0.3 of the first's time.  us per step by rows per tile, the chosen one starred:
+// 512^2 FP32 12.7 (2) 11.5* (3) 12.2 (4) 12.5 (5) 13.1 (6); 1024 x 512 FP32 18.5 (4) 18.0*
+// (5) 18.7 (6) 19.2 (8); 1000^2 FP16 23.5 (4) 20.3 (6) 20.7* (10) 25.6 (16), moment form 24.5
+// (4) 19.0* (6) 20.9 (10) 25.7 (16); 1000^2 FP64 moment form 50.1 (10) 65.9 (16) 42.6* (20) 48.1
+// (24).  FP32 that 16 rows give every SIMD one and a half waves takes them (40
+// lattices of 256 x 128: 47.3 (5) 43.9 (8) 45.8 (10) 38.9* (16) 44.8 (20)).
+//
+// Larger ones: 512-column tiles (256 in FP64), one per compute unit: 4096^2 FP32 0.457 ms
+// (512 x 128) against 0.468 (256 x 64), FP16 0.254 against 0.367; the height whose tiles
+// finish first.
 //
 // Otherwise: the widest tile and tallest segment that still give about sixteen
 // items per compute unit.
@@ -886,10 +891,17 @@ void default_shape(lbb_handle* h)
     if (!h->any_general) {
         const bool mom = is_mom(h->storage);
         if (mom || !h->stream_stores) {
+            const int columns = mom ? lbk::MOM_COLS : lbk::UNIT_COLS;
+            const int share = storage_size(h->storage) == 8 ? 1 : (mom ? 3 : 2);
             h->bx = 64;
-            for (int ly : {16, 8, 4, 2, 1}) {
-                h->ly = ly;
-                if (items(mom ? lbk::MOM_COLS : lbk::UNIT_COLS, ly) >= (mom ? 8 : 4) * ncu) return;
+            h->ly = 16;
+            if (h->storage == LB_F32 && items(columns, 16) >= 6 * ncu) return;
+            long long best = -1;
+            for (int ly = 32; ly >= 1; --ly) {
+                const long long k = (items(columns, ly) + 4 * ncu - 1) / (4 * ncu);   // waves of a SIMD
+                const long long full = k / share, rest = k % share;
+                const long long t = (ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0));
+                if (best < 0 || t < best) { best = t; h->ly = ly; }
             }
             return;
         }
