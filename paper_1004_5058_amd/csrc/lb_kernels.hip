@@ -1273,17 +1273,38 @@ k_stress_reduce(char* __restrict__ base, const LatDesc* __restrict__ descs, doub
     }
 }
 
-// out[y] = sum over the 64-column groups of the profile accumulator.
-__global__ void k_profile_reduce(char* __restrict__ base, const LatDesc* __restrict__ dd,
-                                 double* __restrict__ out)
+// out[y] = sum over the groups of the profile accumulator, in their order.  A block
+// takes 64 rows y; its waves fetch 128 groups into LDS at once and the first adds
+// them up one after the other, so that the order costs no memory latency (a thread
+// that read its groups in turn took 26 us over a 2048 x 1024 lattice's, this 4).
+constexpr int PR_WAVES = 16, PR_GROUPS = 128;
+__global__ void __launch_bounds__(64 * PR_WAVES)
+k_profile_reduce(char* __restrict__ base, const LatDesc* __restrict__ dd, double* __restrict__ out)
 {
+    __shared__ double rows[PR_GROUPS][64];
     const LatDesc& d = *dd;
     const double* pr = (const double*)(base + d.off_prof);
-    for (int y = blockIdx.x * blockDim.x + threadIdx.x; y < d.ny; y += gridDim.x * blockDim.x) {
-        double s = 0;
-        for (int g = 0; g < d.ngroups + d.ngroups2; ++g) s += pr[(long long)g * d.ny + y];
-        out[y] = s;
+    const int w = threadIdx.x >> 6, j = threadIdx.x & 63, ny = d.ny, ng = d.ngroups + d.ngroups2;
+    const int y = blockIdx.x * 64 + j;
+    double s = 0;
+    for (int g0 = 0; g0 < ng; g0 += PR_GROUPS) {
+        double x[PR_GROUPS / PR_WAVES];
+#pragma unroll
+        for (int i = 0; i < PR_GROUPS / PR_WAVES; ++i) {
+            const int g = g0 + i * PR_WAVES + w;
+            x[i] = (g < ng && y < ny) ? pr[(long long)g * ny + y] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < PR_GROUPS / PR_WAVES; ++i) rows[i * PR_WAVES + w][j] = x[i];
+        __syncthreads();
+        if (w == 0) {
+            const int n = min(PR_GROUPS, ng - g0);
+#pragma unroll 16
+            for (int g = 0; g < n; ++g) s += rows[g][j];
+        }
+        __syncthreads();
     }
+    if (w == 0 && y < ny) out[y] = s;
 }
 
 __global__ void k_fill(double* __restrict__ p, long long n, double v)
@@ -1767,7 +1788,7 @@ hipError_t launch_stress_reduce(char* base, const LatDesc* descs, int nlat, doub
 
 hipError_t launch_profile_reduce(char* base, const LatDesc* d, int ny, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_profile_reduce, dim3(grid_for(ny, 256)), dim3(256), 0, s, base, d, out);
+    hipLaunchKernelGGL(k_profile_reduce, dim3((ny + 63) / 64), dim3(64 * PR_WAVES), 0, s, base, d, out);
     return hipGetLastError();
 }
 
