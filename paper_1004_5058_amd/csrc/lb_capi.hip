@@ -97,10 +97,15 @@ lb_status validate(const lb_params* p, int storage0)
 
 // tau is 1 in the storage's arithmetic type: the collision replaces every
 // population by its equilibrium, and the lattice runs the kernels of lb_unit.hip.
+// Their sums round differently, which 16-bit storage turns into a rounding of its own
+// at every step: in BF16 a velocity component moves by 1 to 2 % of itself, in FP16 the
+// accumulated line profile and wall stress by 0.1 to 0.3 % (neither further from FP64
+// than before).  BF16, and FP16 lattices that accumulate a profile, which are
+// measurements, keep the general kernels and so their results to the bit; what that costs
+// is 0.24 against 0.175 ms per step at 4096^2 FP16.
 bool unit_tau(const lb_params& p)
 {
-    // (BF16: the general kernels, whose roundings its results follow)
-    if (p.storage == LB_BF16DEV) return false;
+    if (p.storage == LB_BF16DEV || (p.storage == LB_F16DEV && p.profile)) return false;
     return p.storage == LB_F64 ? p.tau == 1.0 : (float)p.tau == 1.0f && (float)(1.0 / p.tau) == 1.0f;
 }
 
@@ -271,6 +276,8 @@ struct lbb_handle {
     int cur = 0;                     // buffer holding f(t)
     int64_t t = 0, nsamples = 0;
     int bx = 256, ly = 64, grid = 0; // grid 0: one block per tile
+    int pass = 1;                    // time steps per pass in effect (pass_steps)
+    bool shape_set = false;          // by the caller or the tuner, not default_shape
     int ntot = 0;
     int ly_max = 1;                  // largest rows-per-tile over the lattices
     int graph_steps = 32;
@@ -450,6 +457,21 @@ int auto_fnw(const lbb_handle* h)
     return best;
 }
 
+// Time steps per pass in effect.  Two steps a pass, left to choose their tiles, are
+// two launches of the single-step kernel where these are faster: small lattices at
+// tau = 1, of which a fused tile's twelve ticks of overlap are the larger part (the
+// results are the same bits).  us per step of fused and single, FP32: 200^2 9.2, 7.1;
+// 512^2 13.0, 11.9; 600^2 15.2, 14.7; 640^2 15.4, 15.8; 900^2 20.2, 26.7; FP16: 512^2 12.6,
+// 11.1; 640^2 13.9, 13.3; 700^2 14.5, 14.7; 1024^2 20.2, 22.2.  A caller's or the tuner's
+// tile, width or shape is run as it was set.
+int pass_steps(const lbb_handle* h)
+{
+    if (h->fusion != 2 || h->any_general || h->shape_set || h->ly2 > 0 || h->fnw > 0) return h->fusion;
+    long long sites = 0;
+    for (const Lat& a : h->lats) sites += (long long)a.p.nx * a.p.ny;
+    return sites < (long long)device_cus() * (h->storage == LB_F32 ? 1536 : 2048) ? 1 : 2;
+}
+
 // Work decomposition for launch shape (bx, ly): tiles per lattice, and the
 // item -> lattice table the step kernel reads.
 lb_status decompose(lbb_handle* h)
@@ -499,6 +521,7 @@ lb_status decompose(lbb_handle* h)
     }
     if (item2 > h->lay.max_items2) return fail(LB_EINVAL, "fused tile height gives more work items than planned");
     h->ntot2 = item2;
+    h->pass = pass_steps(h);
     HIP_TRY(hipMemcpyAsync(h->d_desc(), h->descs.data(), sizeof(lbk::LatDesc) * h->descs.size(),
                            hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->d_tiles(), h->tiles.data(), sizeof(int32_t) * h->tiles.size(),
@@ -553,7 +576,7 @@ lb_status build_graph(lbb_handle* h, int start)
     HIP_TRY(hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
     lb_status st = LB_OK;
     int src = start;
-    if (h->fusion == 2) {
+    if (h->pass == 2) {
         for (int k = 0; k < h->graph_steps / 2 && st == LB_OK; ++k) {
             st = launch_two(h, h->capture, src);
             src ^= 1;
@@ -618,7 +641,7 @@ lb_status steps(lbb_handle* h, int32_t n)
                 HIP_TRY(hipGraphLaunch(h->exec[h->cur], h->stream));
                 // graph_steps is even: single steps leave the buffer parity
                 // unchanged, fused pairs flip it once per pair
-                if (h->fusion == 2 && ((h->graph_steps / 2) & 1)) {
+                if (h->pass == 2 && ((h->graph_steps / 2) & 1)) {
                     h->cur ^= 1;
                     if (r + 1 < reps && !h->exec[h->cur]) {
                         lb_status st = build_graph(h, h->cur);
@@ -632,7 +655,7 @@ lb_status steps(lbb_handle* h, int32_t n)
             n -= done;
             chunk -= done;
         }
-        if (h->fusion == 2) {
+        if (h->pass == 2) {
             for (; chunk >= 2; chunk -= 2, n -= 2) {
                 lb_status st = launch_two(h, h->stream, h->cur);
                 if (st != LB_OK) return st;
@@ -969,6 +992,7 @@ lb_status set_launch(lbb_handle* h, int bx, int ly, int grid)
     if (bx) h->bx = bx;
     if (ly) h->ly = ly;
     h->grid = grid;
+    h->shape_set = true;
     return decompose(h);
 }
 
@@ -1148,6 +1172,7 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     const int64_t t = h->t, ns = h->nsamples;
     const int bx0 = h->bx, ly0 = h->ly, grid0 = h->grid, gs0 = h->graph_steps, wd0 = h->watchdog;
     const int fu0 = h->fusion, ly20 = h->ly2, fnw0 = h->fnw;
+    const bool set0 = h->shape_set;
     h->graph_steps = 0;
     h->watchdog = 0;
     h->fusion = 1;          // the single-step kernel's shapes are what is tuned
@@ -1270,6 +1295,8 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     h->watchdog = wd0;
     if (st != LB_OK) {
         (void)set_launch(h, bx0, ly0, grid0);
+        h->shape_set = set0;
+        (void)decompose(h);
         return st;
     }
     st = set_launch(h, best.bx, best.ly, best.grid);

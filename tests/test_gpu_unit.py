@@ -54,7 +54,8 @@ CASES = [("f64", bx, 0) for bx in (64, 128, 256)] + [("f32", bx, 0) for bx in (6
                                          (183, 17, False), (257, 9, True), (513, 26, True)])
 def test_tile_edges_match_oracle(storage, bx, lanes, nx, ny, walls):
     ra, rb, u, p, g, mean = _oracle(nx, ny, walls)
-    lat = gpu_lattice(nx, ny, ra, rb, walls=walls, u_top=u, u_bot=-u, storage=storage, profile=True)
+    profile = storage != "f16dev"         # (with a profile FP16 runs the general kernels)
+    lat = gpu_lattice(nx, ny, ra, rb, walls=walls, u_top=u, u_bot=-u, storage=storage, profile=profile)
     lat.set_launch(bx, 11)
     if lanes:
         lat.set_fusion_tile(lanes)
@@ -62,9 +63,10 @@ def test_tile_edges_match_oracle(storage, bx, lanes, nx, ny, walls):
     lat.step(12)
     tol = TOL[storage]
     compare_fields(lat, p, g, tol)
-    prof, n = lat.profile()
-    assert n == 12
-    assert np.max(np.abs(prof - mean)) <= tol
+    if profile:
+        prof, n = lat.profile()
+        assert n == 12
+        assert np.max(np.abs(prof - mean)) <= tol
     lat.close()
 
 
