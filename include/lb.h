@@ -193,9 +193,9 @@ lb_status lb_set_graph(lb_handle* h, int32_t steps_per_graph);
  * the device runs at once at h + 8 ticks per tile of h rows (h + 12 where every
  * lattice's tau is 1), finish first.
  * Results are bitwise independent of the tiles.  With ly2 = 0, the automatic
- * width and no launch shape set or tuned, a small state whose lattices are all at
- * tau = 1 (not BF16, nor FP16 with a profile) is stepped by the single-step kernel where that is faster (up to 1536
- * sites per compute unit in FP32, 2048 in FP16).  LB_EINVAL unless the storage
+ * width and no launch shape set or tuned, a small state is stepped by the
+ * single-step kernel where that is faster (up to 1280 sites per compute unit;
+ * lattices all at tau = 1: 1536 in FP32, 2048 in FP16 without a profile).  LB_EINVAL unless the storage
  * is LB_F32, LB_F16DEV or LB_BF16DEV and the device grants the kernel's
  * shared memory. */
 lb_status lb_set_fusion(lb_handle* h, int32_t steps_per_pass, int32_t ly2);

@@ -458,18 +458,19 @@ int auto_fnw(const lbb_handle* h)
 }
 
 // Time steps per pass in effect.  Two steps a pass, left to choose their tiles, are
-// two launches of the single-step kernel where these are faster: small lattices at
-// tau = 1, of which a fused tile's twelve ticks of overlap are the larger part (the
-// results are the same bits).  us per step of fused and single, FP32: 200^2 9.2, 7.1;
-// 512^2 13.0, 11.9; 600^2 15.2, 14.7; 640^2 15.4, 15.8; 900^2 20.2, 26.7; FP16: 512^2 12.6,
-// 11.1; 640^2 13.9, 13.3; 700^2 14.5, 14.7; 1024^2 20.2, 22.2.  A caller's or the tuner's
-// tile, width or shape is run as it was set.
+// two launches of the single-step kernel where these are faster: small lattices, of
+// which a fused tile's rows of overlap are the larger part (the results are the same
+// bits).  us per step of fused and single, tau = 1 FP32: 200^2 9.2, 7.1; 512^2 13.0, 11.9;
+// 600^2 15.2, 14.7; 640^2 15.4, 15.8; 900^2 20.2, 26.7; FP16: 512^2 12.6, 11.1; 640^2 13.9, 13.3;
+// 700^2 14.5, 14.7; 1024^2 20.2, 22.2; general kernels FP32: 300 x 200 11.6, 9.1; 512^2 15.9,
+// 15.0; 640^2 18.2, 19.5; BF16: 300 x 200 11.7, 8.9; 512^2 16.2, 14.0; 640^2 16.9, 18.2.
+// A caller's or the tuner's tile, width or shape is run as it was set.
 int pass_steps(const lbb_handle* h)
 {
-    if (h->fusion != 2 || h->any_general || h->shape_set || h->ly2 > 0 || h->fnw > 0) return h->fusion;
+    if (h->fusion != 2 || h->shape_set || h->ly2 > 0 || h->fnw > 0) return h->fusion;
     long long sites = 0;
     for (const Lat& a : h->lats) sites += (long long)a.p.nx * a.p.ny;
-    return sites < (long long)device_cus() * (h->storage == LB_F32 ? 1536 : 2048) ? 1 : 2;
+    return sites < (long long)device_cus() * (h->any_general ? 1280 : (h->storage == LB_F32 ? 1536 : 2048)) ? 1 : 2;
 }
 
 // Work decomposition for launch shape (bx, ly): tiles per lattice, and the
@@ -899,7 +900,10 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
 // finish first.
 //
 // Otherwise: the widest tile and tallest segment that still give about sixteen
-// items per compute unit.
+// items per compute unit, or where none does 64-lane tiles of the height that models
+// fastest, as above.  us per step by rows per tile: 128 x 100 BF16 7.3* (1) 8.9 (2) 19.6 (8);
+// 519 x 376 FP32 17.4 (1) 13.2* (2) 14.3 (3) 15.3 (4) 21.0 (8); 777 x 333 FP32 16.4 (2)
+// 15.4* (3) 16.8 (4) 21.9 (8); 1000 x 700 FP64 56.9 (8) 45.6* (12) 49.7 (16).
 void default_shape(lbb_handle* h)
 {
     const long long ncu = device_cus();
@@ -911,21 +915,26 @@ void default_shape(lbb_handle* h)
             n += (long long)((a.p.nx + columns - 1) / columns) * ((a.p.ny + rows - 1) / rows);
         return n;
     };
+    // the height of 64-lane tiles that models fastest (see above)
+    auto model = [&](int columns, int share, int tallest) {
+        long long best = -1;
+        h->bx = 64;
+        for (int ly = tallest; ly >= 1; --ly) {
+            const long long k = (items(columns, ly) + 4 * ncu - 1) / (4 * ncu);   // waves of a SIMD
+            const long long full = k / share, rest = k % share;
+            const long long t = (ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0));
+            if (best < 0 || t < best) { best = t; h->ly = ly; }
+        }
+    };
+    const bool mom = is_mom(h->storage);
+    const int share = storage_size(h->storage) == 8 ? 1 : (mom ? 3 : 2);
     if (!h->any_general) {
-        const bool mom = is_mom(h->storage);
         if (mom || !h->stream_stores) {
             const int columns = mom ? lbk::MOM_COLS : lbk::UNIT_COLS;
-            const int share = storage_size(h->storage) == 8 ? 1 : (mom ? 3 : 2);
             h->bx = 64;
             h->ly = 16;
             if (h->storage == LB_F32 && items(columns, 16) >= 6 * ncu) return;
-            long long best = -1;
-            for (int ly = 32; ly >= 1; --ly) {
-                const long long k = (items(columns, ly) + 4 * ncu - 1) / (4 * ncu);   // waves of a SIMD
-                const long long full = k / share, rest = k % share;
-                const long long t = (ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0));
-                if (best < 0 || t < best) { best = t; h->ly = ly; }
-            }
+            model(columns, share, 32);
             return;
         }
         h->bx = h->storage == LB_F64 ? 256 : 512;
@@ -945,6 +954,7 @@ void default_shape(lbb_handle* h)
         h->ly = c[1];
         if (items(c[0], c[1]) >= 16 * ncu) return;
     }
+    model(64, share, 16);
 }
 
 // Tile widths with a step kernel: 64, 128, 256, and 512 for the FP32 and
