@@ -1,7 +1,10 @@
 // HIP kernels (gfx950) of the time step at tau = 1: the step of lb_kernels.hip
 // where the BGK collision of Eq. (1) replaces every population by the
-// equilibrium at the shifted velocity, f*_is = f^eq_i(rho_s, v_s).  Every
-// storage format runs these kernels at tau = 1 (the moment form always does).
+// equilibrium at the shifted velocity, f*_is = f^eq_i(rho_s, v_s).  FP64, FP32, the
+// moment form and, without a line profile, FP16 run these kernels at tau = 1 (BF16
+// and FP16 profiles keep the roundings of the general ones).  Per step before and
+// now: 4096^2 FP32 in pairs 0.286 -> 0.262 ms, FP16 0.220 -> 0.174, moment form 0.258 ->
+// 0.194; 128^2 FP64 20 -> 8.7 us; 512^2 FP32 in pairs 19 -> 13 us, single steps 11.8.
 //
 // What tau = 1 saves.  Nothing of a row's populations is needed past its four
 // sums (the two density deviations and the momentum), so a row leaves the
@@ -779,7 +782,7 @@ k_step_unit_wide(char* __restrict__ base, const LatDesc* __restrict__ descs, con
 // step the initial state itself, read in place).  As k_step_unit, but a loaded
 // row is the post-collision state: each lane forms its column's eighteen
 // populations once, sums them by direction as they stream (Flow) and takes the
-// neighbours' three values per x direction by lane shifts.  58 columns a wave
+// neighbours' values per x direction by lane shifts.  58 columns a wave
 // (one more each side than the populations' step).
 template <int BX, class P>
 __global__ void __launch_bounds__(BX)
@@ -921,11 +924,12 @@ k_step_mom(char* __restrict__ base, const LatDesc* __restrict__ descs, const int
 // and one of streaming for each step, less the outermost of step t's streaming).
 //
 // What bounds it: the issue rate of a wave at few waves per SIMD, so the registers.
-// A half keeps one belt of rows and one row of loads in 128 registers: four waves
-// per SIMD (both steps in one thread took 241 registers and ran two waves of twice
-// the work: 14.6 against 11.1 us per step at 512^2).  Between the steps nine sums
-// per column cross LDS instead of eighteen populations of nine rows (43 against
-// 103 KB a block of 256 FP32 lanes).
+// A half keeps one belt of rows and one or two rows of loads in 195 (FP32) or 159
+// (FP16) registers, two and three waves per SIMD; both steps in one thread took 241
+// and ran twice the work in each.  Between the steps eleven sums per column cross
+// LDS instead of eighteen populations of nine rows.  FP32 runs best at 182 columns and
+// six waves a compute unit (4096^2: 0.262 ms a step; 246 columns, eight waves: 0.274;
+// 118 columns, two blocks of four: 0.31), FP16 at 118 in three blocks (0.174; 246: 0.20).
 template <class P> constexpr int FUSE_MIN_WAVES = sizeof(typename P::S) == 4 ? 2 : 3;
 template <class P, int NW, int TW, int PW>
 __global__ void __launch_bounds__(128 * NW, FUSE_MIN_WAVES<P>)
