@@ -93,3 +93,22 @@ def test_checkpoint_with_fewer_profile_rows(storage, width):
     np.testing.assert_allclose(other.profile()[0], want, rtol=1e-14, atol=0)
     other.close()
     lat.close()
+
+
+@pytest.mark.parametrize("storage,tau", [("f32", 1.0), ("f16dev", 1.0), ("f32", 1.2), ("bf16dev", 1.0)])
+def test_pairs_left_to_choose_equal_set_tiles(storage, tau):
+    """Two steps a pass of a small lattice: the library's own choice (single steps)
+    against a set tile (the fused kernel), across graph replays and an odd remainder."""
+    ra, rb, u, *_ = _oracle(183, 17, False)
+    pops = []
+    for ly2 in (0, 6):
+        lat = gpu_lattice(183, 17, ra, rb, walls=False, storage=storage, tau=tau)
+        lat.set_graph(6)
+        lat.set_fusion(2, ly2)
+        assert lat.launch()["steps_per_pass"] == 2
+        lat.step(8)
+        lat.step(15)
+        assert lat.time() == 23
+        pops.append(lat.populations())
+        lat.close()
+    np.testing.assert_array_equal(pops[0], pops[1])
