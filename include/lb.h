@@ -167,8 +167,8 @@ lb_status lb_set_watchdog(lb_handle* h, int32_t every);
 
 /* Launch shape of the step kernel: bx lattice columns per tile (64, 128 or 256,
  * and 512 for FP32 and 16-bit population storage), ly rows per tile (>= 1).  At
- * tau = 1 a tile of bx = 64 is one wave that stores 60 columns, and the moment
- * form stores 58 columns per 64 of bx (each wave overlaps its neighbours).  0
+ * tau = 1 in FP64 and FP32 a tile of bx = 64 is one wave that stores 60 columns,
+ * and the moment form stores 58 columns per 64 of bx (each wave overlaps its neighbours).  0
  * keeps the current choice.  LB_EINVAL for another bx or for a shape whose
  * shared memory per block (it grows with bx and ly) exceeds the device's limit.
  * Results are bitwise independent of the shape. */
@@ -190,21 +190,20 @@ lb_status lb_set_graph(lb_handle* h, int32_t steps_per_graph);
  * segments of near-equal height, one more while they would all be the same
  * multiple of 16 rows; a batch hands out its lattices' tiles tallest segments
  * first.  ly2 = 0: the height whose tiles, handed out greedily to the blocks
- * the device runs at once at h + 8 ticks per tile of h rows (h + 12 where every
- * lattice's tau is 1), finish first.
+ * the device runs at once at h + 8 ticks per tile of h rows (h + 12 for FP32
+ * lattices all at tau = 1), finish first.
  * Results are bitwise independent of the tiles.  With ly2 = 0, the automatic
  * width and no launch shape set or tuned, a small state is stepped by the
  * single-step kernel where that is faster (up to 1280 sites per compute unit;
- * lattices all at tau = 1: 1536 in FP32, 2048 in FP16 without a profile).  LB_EINVAL unless the storage
- * is LB_F32, LB_F16DEV or LB_BF16DEV and the device grants the kernel's
+ * FP32 lattices all at tau = 1: 1536).  LB_EINVAL unless the storage is LB_F32, LB_F16DEV or LB_BF16DEV and the device grants the kernel's
  * shared memory. */
 lb_status lb_set_fusion(lb_handle* h, int32_t steps_per_pass, int32_t ly2);
 
 /* Block width of the two-steps-per-pass kernel: lanes = 128, 192 or 256
  * threads per time step (the block has twice as many; FP32 at 128 lanes and
  * tau = 1 takes 192 for its columns and their overlap), or 0 for the width
- * with the most waves resident per compute unit (tau = 1: the least time for
- * the lattices' strips).  A tile stores lanes - 6
+ * with the most waves resident per compute unit (FP32 all at tau = 1: the least
+ * time for the lattices' strips).  A tile stores lanes - 6
  * columns (FP32 at 128 lanes) or lanes - 10 (the other widths and the 16-bit
  * forms): the step-t columns beyond them are the overlap step t+1 needs (for
  * lanes - 10 also the two columns each side whose densities step t's stencil

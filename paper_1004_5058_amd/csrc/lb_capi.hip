@@ -97,15 +97,14 @@ lb_status validate(const lb_params* p, int storage0)
 
 // tau is 1 in the storage's arithmetic type: the collision replaces every
 // population by its equilibrium, and the lattice runs the kernels of lb_unit.hip.
-// Their sums round differently, which 16-bit storage turns into a rounding of its own
-// at every step: in BF16 a velocity component moves by 1 to 2 % of itself, in FP16 the
-// accumulated line profile and wall stress by 0.1 to 0.3 % (neither further from FP64
-// than before).  BF16, and FP16 lattices that accumulate a profile, which are
-// measurements, keep the general kernels and so their results to the bit; what that costs
-// is 0.24 against 0.175 ms per step at 4096^2 FP16.
+// 16-bit storage stays with the general ones: the sums of those kernels round
+// differently, which 16 bits turn into a rounding of their own at every step (no
+// further from FP64, but a velocity component moves by 1 to 2 % of itself in BF16 and
+// by 0.2 % in FP16, an accumulated profile or wall stress by 0.1 to 0.3 %).  FP16 would
+// run in 0.175 instead of 0.22 ms per step at 4096^2.
 bool unit_tau(const lb_params& p)
 {
-    if (p.storage == LB_BF16DEV || (p.storage == LB_F16DEV && p.profile)) return false;
+    if (p.storage == LB_F16DEV || p.storage == LB_BF16DEV) return false;
     return p.storage == LB_F64 ? p.tau == 1.0 : (float)p.tau == 1.0f && (float)(1.0 / p.tau) == 1.0f;
 }
 
@@ -437,10 +436,9 @@ int auto_fnw(const lbb_handle* h)
     if (!fusion_storage(h->storage)) return best;
     if (!h->any_general) {
         // tau = 1: the least strips x rows, weighted by what a row of a strip of each
-        // width costs (4096^2: FP32 0.317, 0.263 and 0.271 ms per step at 128, 192 and
-        // 256 lanes, FP16 0.175, 0.239 and 0.192, times the strip's columns)
-        static const int cost[2][5] = {{0, 0, 39, 48, 67}, {0, 0, 21, 44, 47}};
-        const int* c = cost[h->storage == LB_F32 ? 0 : 1];
+        // width costs (4096^2 FP32: 0.317, 0.263 and 0.271 ms per step at 128, 192 and 256
+        // lanes, times the strip's columns)
+        static const int c[5] = {0, 0, 39, 48, 67};
         long long best_t = -1;
         for (int nw : {2, 3, 4}) {
             const int tw = lbk::fuse2_tw(h->storage, nw);
@@ -461,8 +459,7 @@ int auto_fnw(const lbb_handle* h)
 // two launches of the single-step kernel where these are faster: small lattices, of
 // which a fused tile's rows of overlap are the larger part (the results are the same
 // bits).  us per step of fused and single, tau = 1 FP32: 200^2 9.2, 7.1; 512^2 13.0, 11.9;
-// 600^2 15.2, 14.7; 640^2 15.4, 15.8; 900^2 20.2, 26.7; FP16: 512^2 12.6, 11.1; 640^2 13.9, 13.3;
-// 700^2 14.5, 14.7; 1024^2 20.2, 22.2; general kernels FP32: 300 x 200 11.6, 9.1; 512^2 15.9,
+// 600^2 15.2, 14.7; 640^2 15.4, 15.8; 900^2 20.2, 26.7; general kernels FP32: 300 x 200 11.6, 9.1; 512^2 15.9,
 // 15.0; 640^2 18.2, 19.5; BF16: 300 x 200 11.7, 8.9; 512^2 16.2, 14.0; 640^2 16.9, 18.2.
 // A caller's or the tuner's tile, width or shape is run as it was set.
 int pass_steps(const lbb_handle* h)
@@ -470,7 +467,7 @@ int pass_steps(const lbb_handle* h)
     if (h->fusion != 2 || h->shape_set || h->ly2 > 0 || h->fnw > 0) return h->fusion;
     long long sites = 0;
     for (const Lat& a : h->lats) sites += (long long)a.p.nx * a.p.ny;
-    return sites < (long long)device_cus() * (h->any_general ? 1280 : (h->storage == LB_F32 ? 1536 : 2048)) ? 1 : 2;
+    return sites < (long long)device_cus() * (h->any_general ? 1280 : 1536) ? 1 : 2;
 }
 
 // Work decomposition for launch shape (bx, ly): tiles per lattice, and the
@@ -887,17 +884,16 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
 //
 // tau = 1 and moment form, lattices that stay in the caches: one-wave tiles of the
 // height that models fastest: a tile of ly rows takes ly + 3 row times, up to three
-// (moment form; 16-bit and FP32: two, FP64: one) waves of a SIMD share it, each further one
+// (moment form; FP32: two, FP64: one) waves of a SIMD share it, each further one
 // adding 0.3 of the first's time.  us per step by rows per tile, the chosen one starred:
 // 512^2 FP32 12.7 (2) 11.5* (3) 12.2 (4) 12.5 (5) 13.1 (6); 1024 x 512 FP32 18.5 (4) 18.0*
-// (5) 18.7 (6) 19.2 (8); 1000^2 FP16 23.5 (4) 20.3 (6) 20.7* (10) 25.6 (16), moment form 24.5
+// (5) 18.7 (6) 19.2 (8); 1000^2 moment form 24.5
 // (4) 19.0* (6) 20.9 (10) 25.7 (16); 1000^2 FP64 moment form 50.1 (10) 65.9 (16) 42.6* (20) 48.1
 // (24).  FP32 that 16 rows give every SIMD one and a half waves takes them (40
 // lattices of 256 x 128: 47.3 (5) 43.9 (8) 45.8 (10) 38.9* (16) 44.8 (20)).
 //
 // Larger ones: 512-column tiles (256 in FP64), one per compute unit: 4096^2 FP32 0.457 ms
-// (512 x 128) against 0.468 (256 x 64), FP16 0.254 against 0.367; the height whose tiles
-// finish first.
+// (512 x 128) against 0.468 (256 x 64); the height whose tiles finish first.
 //
 // Otherwise: the widest tile and tallest segment that still give about sixteen
 // items per compute unit, or where none does 64-lane tiles of the height that models

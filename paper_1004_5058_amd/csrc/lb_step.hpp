@@ -258,28 +258,6 @@ template <class P> struct Row<P, true> {
     {
         return mix_pair<QA & 1, QB & 1, NEG>(u<QA>(), u<QB>());
     }
-    template <int QA, int QB, bool NEG = false> __device__ __forceinline__ float two() const
-    {
-        if constexpr (MIX) return pair<QA, QB, NEG>();
-        else return NEG ? (*this)[QA] - (*this)[QB] : (*this)[QA] + (*this)[QB];
-    }
-    template <int Q, bool NEG = false> __device__ __forceinline__ float more(float x) const
-    {
-        if constexpr (MIX) return acc<Q, NEG>(x);
-        else return NEG ? x - (*this)[Q] : x + (*this)[Q];
-    }
-    // rounded to the storage format, each on its own
-    __device__ __forceinline__ void set(const float (&a)[9], const float (&b)[9])
-    {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int q0 = 2 * k, q1 = 2 * k + 1;
-            S lo, hi;
-            to_store2<S>(q0 < 9 ? a[q0 % 9] : b[q0 % 9], q1 < 9 ? a[q1 % 9] : b[q1 % 9], lo, hi);
-            v[k].x = lo;
-            v[k].y = hi;
-        }
-    }
     __device__ __forceinline__ void dens(float& da, float& db) const
     {
         if constexpr (MIX) {

@@ -1,10 +1,9 @@
 // HIP kernels (gfx950) of the time step at tau = 1: the step of lb_kernels.hip
 // where the BGK collision of Eq. (1) replaces every population by the
-// equilibrium at the shifted velocity, f*_is = f^eq_i(rho_s, v_s).  FP64, FP32, the
-// moment form and, without a line profile, FP16 run these kernels at tau = 1 (BF16
-// and FP16 profiles keep the roundings of the general ones).  Per step before and
-// now: 4096^2 FP32 in pairs 0.286 -> 0.262 ms, FP16 0.220 -> 0.174, moment form 0.258 ->
-// 0.194; 128^2 FP64 20 -> 8.7 us; 512^2 FP32 in pairs 19 -> 13 us, single steps 11.8.
+// equilibrium at the shifted velocity, f*_is = f^eq_i(rho_s, v_s).  FP64, FP32 and
+// the moment form run these kernels at tau = 1 (16-bit storage keeps the roundings of
+// the general ones).  Per step before and now: 4096^2 FP32 in pairs 0.286 -> 0.262 ms,
+// moment form 0.258 -> 0.194; 128^2 FP64 20 -> 8.7 us; 512^2 FP32 in pairs 19 -> 13 us, single steps 11.8.
 //
 // What tau = 1 saves.  Nothing of a row's populations is needed past its four
 // sums (the two density deviations and the momentum), so a row leaves the
@@ -108,30 +107,25 @@ template <class C> __device__ __forceinline__ void add_sums(Sums<C>& s, const Su
     s.jy += w.jy;
 }
 
-// The 18 incoming populations of a node as loaded, a register each (summed at
-// once: 16-bit values need no packing), with Row's two and more.
+// The 18 incoming populations of a node as loaded, with Row's two and more.
 template <class P> struct Raw {
-    using S = typename P::S;
-    using C = typename P::C;
-    static constexpr bool MIX = std::is_same<S, _Float16>::value;
-    S v[18];
-    __device__ __forceinline__ C operator[](int q) const { return (C)v[q]; }
+    using C = typename P::C;           // (the storage type too)
+    C v[18];
+    __device__ __forceinline__ C operator[](int q) const { return v[q]; }
     template <int QA, int QB, bool NEG = false> __device__ __forceinline__ C two() const
     {
-        if constexpr (MIX) return mix_pair<0, 0, NEG>(v[QA], v[QB]);
-        else return NEG ? (C)v[QA] - (C)v[QB] : (C)v[QA] + (C)v[QB];
+        return NEG ? v[QA] - v[QB] : v[QA] + v[QB];
     }
     template <int Q, bool NEG = false> __device__ __forceinline__ C more(C x) const
     {
-        if constexpr (MIX) return mix_acc<0, NEG>(v[Q], x);
-        else return NEG ? x - (C)v[Q] : x + (C)v[Q];
+        return NEG ? x - v[Q] : x + v[Q];
     }
     __device__ __forceinline__ void load(rsrc_t r0, rsrc_t r1, unsigned vl, unsigned vc, unsigned vr, unsigned pbytes)
     {
 #pragma unroll
         for (int q = 0; q < 18; ++q) {
             const int cx = CX[q % 9];
-            v[q] = bload<S>(q < 9 ? r0 : r1, cx > 0 ? vl : (cx < 0 ? vr : vc),
+            v[q] = bload<C>(q < 9 ? r0 : r1, cx > 0 ? vl : (cx < 0 ? vr : vc),
                             (unsigned)__builtin_amdgcn_readfirstlane((int)((q % 9) * pbytes)));
         }
     }
@@ -918,28 +912,25 @@ k_step_mom(char* __restrict__ base, const LatDesc* __restrict__ descs, const int
 // published a tick earlier into the next row of step t+1, stages row y0-10+i and
 // collides row y0-12+i, stored to HBM.  One LDS barrier per tick orders the three
 // exchanges (near1 and near2: the staged psi and rho rows; part), each
-// double-buffered.  The arithmetic and its order are k_step_unit's, values between
-// the steps rounded to the storage format, so a pair of steps is bitwise that of
-// two launches.  Five columns each side overlap the neighbouring tiles (two of psi
+// double-buffered.  The arithmetic and its order are k_step_unit's, so a pair of steps
+// is bitwise that of two launches.  Five columns each side overlap the neighbouring tiles (two of psi
 // and one of streaming for each step, less the outermost of step t's streaming).
 //
 // What bounds it: the issue rate of a wave at few waves per SIMD, so the registers.
-// A half keeps one belt of rows and one or two rows of loads in 195 (FP32) or 159
-// (FP16) registers, two and three waves per SIMD; both steps in one thread took 241
-// and ran twice the work in each.  Between the steps eleven sums per column cross
-// LDS instead of eighteen populations of nine rows.  FP32 runs best at 182 columns and
+// A half keeps one belt of rows and two rows of loads in 195 registers, two waves per
+// SIMD; both steps in one thread took 241 and ran twice the work in each.  Between the steps eleven sums per column cross
+// LDS instead of eighteen populations of nine rows.  It runs best at 182 columns and
 // six waves a compute unit (4096^2: 0.262 ms a step; 246 columns, eight waves: 0.274;
-// 118 columns, two blocks of four: 0.31), FP16 at 118 in three blocks (0.174; 246: 0.20).
-template <class P> constexpr int FUSE_MIN_WAVES = sizeof(typename P::S) == 4 ? 2 : 3;
+// 118 columns, two blocks of four: 0.31).
 template <class P, int NW, int TW, int PW>
-__global__ void __launch_bounds__(128 * NW, FUSE_MIN_WAVES<P>)
+__global__ void __launch_bounds__(128 * NW, 2)
 k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
              int src)
 {
     using S = typename P::S;
     using C = typename P::C;
     using C2 = typename V2<C>::T;
-    constexpr int BW = 64 * NW, XO = 5, DEPTH = sizeof(typename P::S) == 4 ? 2 : 1;
+    constexpr int BW = 64 * NW, XO = 5, DEPTH = 2;
     static_assert(TW + 2 * XO <= BW, "every output column and its overlap has a thread");
     // entries j + 2 and j + 1; the outer ones stay zero (they feed no output)
     __shared__ Quad<C> near1[2][BW + 4], near2[2][BW + 4];
@@ -1037,9 +1028,9 @@ k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const i
                     Row<P> q;
                     q.set(ea, eb);
                     done = flow.feed(q);
-                    // the populations a wall returns, rounded as they are stored
+                    // the populations a wall returns
                     auto returned = [&](const C(&e)[9], int s, int i1, WallSpeed<C> uw) {
-                        return (C)to_store<S>(bounced(e[i1], t.r[s], CX[i1], uw));
+                        return bounced(e[i1], t.r[s], CX[i1], uw);
                     };
                     if (near && y == 0) {
                         const Sums<C> v = wall_sums<C>(q[4], returned(ea, 0, 7, k.u_bot), returned(ea, 0, 8, k.u_bot), q[13],
@@ -1163,7 +1154,7 @@ hipError_t unit_p(int bx, char* base, const LatDesc* descs, const int* tiles, in
     case 64: return unit_bx<64, P>(base, descs, tiles, ntot, src, stream, grid, s);
     case 128: return unit_bx<128, P>(base, descs, tiles, ntot, src, stream, grid, s);
     case 256: return unit_bx<256, P>(base, descs, tiles, ntot, src, stream, grid, s);
-    case 512:   // as the general step: 4- and 2-byte storage only
+    case 512:   // as the general step: not FP64
         if constexpr (sizeof(typename P::S) <= 4) return unit_bx<512, P>(base, descs, tiles, ntot, src, stream, grid, s);
         return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
@@ -1188,16 +1179,13 @@ hipError_t mom_p(int bx, char* base, const LatDesc* descs, const int* tiles, int
     }
 }
 
-// The fused kernel of a storage and nw waves of output columns (fuse2_tw); FP32
-// at nw = 2 stores six columns less than its lanes, so its overlap takes a third wave.
+// The fused kernel of a storage and nw waves of output columns (fuse2_tw); nw = 2
+// stores six columns less than its lanes, so its overlap takes a third wave.
 #define LBK_UNIT2_CASES(F)                                                                          \
     switch (storage * 10 + nw) {                                                                     \
     case 12: return F((k_step2_unit<StF32, 3, fuse2_tw(1, 2), 2>), 384);                             \
     case 13: return F((k_step2_unit<StF32, 3, fuse2_tw(1, 3), 3>), 384);                             \
     case 14: return F((k_step2_unit<StF32, 4, fuse2_tw(1, 4), 4>), 512);                             \
-    case 22: return F((k_step2_unit<StF16, 2, fuse2_tw(2, 2), 2>), 256);                             \
-    case 23: return F((k_step2_unit<StF16, 3, fuse2_tw(2, 3), 3>), 384);                             \
-    case 24: return F((k_step2_unit<StF16, 4, fuse2_tw(2, 4), 4>), 512);                             \
     default: break;                                                                                  \
     }
 
@@ -1209,7 +1197,6 @@ hipError_t launch_step_unit(int storage, int bx, char* base, const LatDesc* desc
     switch (storage) {
     case 0: return unit_p<StF64>(bx, base, descs, tiles, ntot, src, stream, grid, s);
     case 1: return unit_p<StF32>(bx, base, descs, tiles, ntot, src, stream, grid, s);
-    case 2: return unit_p<StF16>(bx, base, descs, tiles, ntot, src, stream, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
