@@ -192,10 +192,8 @@ lb_status lb_set_graph(lb_handle* h, int32_t steps_per_graph);
  * first.  ly2 = 0: the height whose tiles, handed out greedily to the blocks
  * the device runs at once at h + 8 ticks per tile of h rows (h + 12 for FP32
  * lattices all at tau = 1), finish first.
- * Results are bitwise independent of the tiles.  With ly2 = 0, the automatic
- * width and no launch shape set or tuned, a small state is stepped by the
- * single-step kernel where that is faster (up to 1280 sites per compute unit;
- * FP32 lattices all at tau = 1: 1536).  LB_EINVAL unless the storage is LB_F32, LB_F16DEV or LB_BF16DEV and the device grants the kernel's
+ * Results are bitwise independent of the tiles.  LB_EINVAL unless the storage
+ * is LB_F32, LB_F16DEV or LB_BF16DEV and the device grants the kernel's
  * shared memory. */
 lb_status lb_set_fusion(lb_handle* h, int32_t steps_per_pass, int32_t ly2);
 

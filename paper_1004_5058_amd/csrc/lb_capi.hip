@@ -275,8 +275,6 @@ struct lbb_handle {
     int cur = 0;                     // buffer holding f(t)
     int64_t t = 0, nsamples = 0;
     int bx = 256, ly = 64, grid = 0; // grid 0: one block per tile
-    int pass = 1;                    // time steps per pass in effect (pass_steps)
-    bool shape_set = false;          // by the caller or the tuner, not default_shape
     int ntot = 0;
     int ly_max = 1;                  // largest rows-per-tile over the lattices
     int graph_steps = 32;
@@ -455,21 +453,6 @@ int auto_fnw(const lbb_handle* h)
     return best;
 }
 
-// Time steps per pass in effect.  Two steps a pass, left to choose their tiles, are
-// two launches of the single-step kernel where these are faster: small lattices, of
-// which a fused tile's rows of overlap are the larger part (the results are the same
-// bits).  us per step of fused and single, tau = 1 FP32: 200^2 9.2, 7.1; 512^2 13.0, 11.9;
-// 600^2 15.2, 14.7; 640^2 15.4, 15.8; 900^2 20.2, 26.7; general kernels FP32: 300 x 200 11.6, 9.1; 512^2 15.9,
-// 15.0; 640^2 18.2, 19.5; BF16: 300 x 200 11.7, 8.9; 512^2 16.2, 14.0; 640^2 16.9, 18.2.
-// A caller's or the tuner's tile, width or shape is run as it was set.
-int pass_steps(const lbb_handle* h)
-{
-    if (h->fusion != 2 || h->shape_set || h->ly2 > 0 || h->fnw > 0) return h->fusion;
-    long long sites = 0;
-    for (const Lat& a : h->lats) sites += (long long)a.p.nx * a.p.ny;
-    return sites < (long long)device_cus() * (h->any_general ? 1280 : 1536) ? 1 : 2;
-}
-
 // Work decomposition for launch shape (bx, ly): tiles per lattice, and the
 // item -> lattice table the step kernel reads.
 lb_status decompose(lbb_handle* h)
@@ -519,7 +502,6 @@ lb_status decompose(lbb_handle* h)
     }
     if (item2 > h->lay.max_items2) return fail(LB_EINVAL, "fused tile height gives more work items than planned");
     h->ntot2 = item2;
-    h->pass = pass_steps(h);
     HIP_TRY(hipMemcpyAsync(h->d_desc(), h->descs.data(), sizeof(lbk::LatDesc) * h->descs.size(),
                            hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->d_tiles(), h->tiles.data(), sizeof(int32_t) * h->tiles.size(),
@@ -574,7 +556,7 @@ lb_status build_graph(lbb_handle* h, int start)
     HIP_TRY(hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
     lb_status st = LB_OK;
     int src = start;
-    if (h->pass == 2) {
+    if (h->fusion == 2) {
         for (int k = 0; k < h->graph_steps / 2 && st == LB_OK; ++k) {
             st = launch_two(h, h->capture, src);
             src ^= 1;
@@ -639,7 +621,7 @@ lb_status steps(lbb_handle* h, int32_t n)
                 HIP_TRY(hipGraphLaunch(h->exec[h->cur], h->stream));
                 // graph_steps is even: single steps leave the buffer parity
                 // unchanged, fused pairs flip it once per pair
-                if (h->pass == 2 && ((h->graph_steps / 2) & 1)) {
+                if (h->fusion == 2 && ((h->graph_steps / 2) & 1)) {
                     h->cur ^= 1;
                     if (r + 1 < reps && !h->exec[h->cur]) {
                         lb_status st = build_graph(h, h->cur);
@@ -653,7 +635,7 @@ lb_status steps(lbb_handle* h, int32_t n)
             n -= done;
             chunk -= done;
         }
-        if (h->pass == 2) {
+        if (h->fusion == 2) {
             for (; chunk >= 2; chunk -= 2, n -= 2) {
                 lb_status st = launch_two(h, h->stream, h->cur);
                 if (st != LB_OK) return st;
@@ -998,7 +980,6 @@ lb_status set_launch(lbb_handle* h, int bx, int ly, int grid)
     if (bx) h->bx = bx;
     if (ly) h->ly = ly;
     h->grid = grid;
-    h->shape_set = true;
     return decompose(h);
 }
 
@@ -1178,7 +1159,6 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     const int64_t t = h->t, ns = h->nsamples;
     const int bx0 = h->bx, ly0 = h->ly, grid0 = h->grid, gs0 = h->graph_steps, wd0 = h->watchdog;
     const int fu0 = h->fusion, ly20 = h->ly2, fnw0 = h->fnw;
-    const bool set0 = h->shape_set;
     h->graph_steps = 0;
     h->watchdog = 0;
     h->fusion = 1;          // the single-step kernel's shapes are what is tuned
@@ -1301,8 +1281,6 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     h->watchdog = wd0;
     if (st != LB_OK) {
         (void)set_launch(h, bx0, ly0, grid0);
-        h->shape_set = set0;
-        (void)decompose(h);
         return st;
     }
     st = set_launch(h, best.bx, best.ly, best.grid);
