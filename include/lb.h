@@ -228,18 +228,21 @@ lb_status lb_save(lb_handle* h, void* buf, size_t* bytes);
 lb_status lb_load(lb_handle* h, const void* buf, size_t bytes);
 
 /* Autotuner: after about 0.3 s of steps to bring the GPU's clocks up, times
- * `steps` steps of every candidate launch shape (bx in {64, 128, 256, 512} as
- * lb_set_launch admits them, ly in {8..256}, shapes within the device's shared
- * memory per block; for batches also persistent grids of 1, 2 and 4 blocks
- * per compute unit) on this lattice; where lb_set_fusion admits two steps per
+ * `steps` steps of every candidate launch shape (the handle's own and the default
+ * if of at least 8 rows; bx in {64, 128, 256, 512} as lb_set_launch admits them,
+ * ly in {8..256}, shapes within the device's shared memory per block; for batches
+ * also persistent grids of 1, 2 and 4 blocks per compute unit) on this lattice; where lb_set_fusion admits two steps per
  * pass (FP32, 16-bit), also that mode behind the best shape, for each block
  * width of lb_set_fusion_tile the device grants, at the automatic tile height
  * and at heights of 20 to 300 rows (odd multiples of 4); then times the four
  * fastest candidates twice more over 4 x steps steps.  Applies the fastest of
- * those (shape, steps per pass and fused width; *ms is its time per step) and
- * restores the simulation state exactly (populations, accumulators, step
+ * those (shape, steps per pass and fused width; *ms is its time per step) or,
+ * where single steps in a default shape of fewer than 8 rows (small lattices) are
+ * faster by 5 %, these: the entry then says "default": 1, *ms is their time,
+ * *bx and *ly remain the fastest candidate's and lb_get_launch tells the shape in
+ * effect.  Restores the simulation state exactly (populations, accumulators, step
  * count).  cache_path (may be NULL): JSON file of {key: {bx, ly, grid,
- * fusion, ly2, fw, ms}}, key "<gfx arch>/<storage>/<nx>x<ny>" (batches:
+ * fusion, ly2, fw, [default,] ms}}, key "<gfx arch>/<storage>/<nx>x<ny>" (batches:
  * "batch<n>_<sites>"); a cached entry is applied without timing (its fusion
  * only where admitted; entries without it mean one step per pass, without fw
  * the automatic width), a new result is added.  Synchronises.  Allocates a

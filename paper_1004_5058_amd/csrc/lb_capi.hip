@@ -859,10 +859,10 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
     return LB_OK;
 }
 
-// Default launch shape.  A block marches its segment row by row and each row
-// waits on memory, so small lattices and small batches split into a few tall
-// items leave the chip idle; big lattices keep wide, tall items (fewer segment
-// prologues and halo columns).
+// Default launch shape (sets bx, ly and grid).  A block marches its segment row by
+// row and each row waits on memory, so small lattices and small batches split into
+// a few tall items leave the chip idle; big lattices keep wide, tall items (fewer
+// segment prologues and halo columns).
 //
 // tau = 1 and moment form, lattices that stay in the caches: one-wave tiles of the
 // height that models fastest: a tile of ly rows takes ly + 3 row times, up to three
@@ -886,6 +886,7 @@ void default_shape(lbb_handle* h)
 {
     const long long ncu = device_cus();
     int maxnx = 0;
+    h->grid = 0;
     for (const Lat& a : h->lats) maxnx = std::max(maxnx, a.p.nx);
     auto items = [&](int columns, int rows) {
         long long n = 0;
@@ -1117,6 +1118,14 @@ lb_status write_cache(const char* path, const lbh::TuneCache& ents)
     return LB_OK;
 }
 
+// The single-step shape of a tuned entry.
+lb_status apply_shape(lbb_handle* h, const TuneEntry& e)
+{
+    if (!e.dflt) return set_launch(h, e.bx, e.ly, e.grid);
+    default_shape(h);
+    return decompose(h);
+}
+
 lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch, TuneEntry* best_out)
 {
     if (steps < 1) return fail(LB_EINVAL, "need steps >= 1");
@@ -1124,8 +1133,12 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     auto cache = lbh::read_cache(cache_path);
     for (auto& kv : cache)
         if (kv.first == key && kv.second.bx) {
-            lb_status st = set_launch(h, kv.second.bx, kv.second.ly, kv.second.grid);
+            lb_status st = apply_shape(h, kv.second);
             if (st != LB_OK) return st;
+            if (kv.second.dflt) {
+                if (best_out) *best_out = kv.second;
+                return set_fusion(h, 1, 0);
+            }
             const bool fuse = kv.second.fusion == 2 && fusion_allowed(h);
             if (fuse) {
                 st = set_fusion_tile(h, kv.second.fw);
@@ -1187,7 +1200,7 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
         }
     }
     auto time_entry = [&](TuneEntry& e, int n) -> lb_status {
-        lb_status s2 = set_launch(h, e.bx, e.ly, e.grid);
+        lb_status s2 = apply_shape(h, e);
         if (s2 == LB_OK && e.fusion == 2) s2 = set_fusion_tile(h, e.fw);
         if (s2 == LB_OK) s2 = set_fusion(h, e.fusion, e.fusion == 2 ? e.ly2 : 0);
         if (s2 == LB_OK) s2 = steps_direct_warm(h, 2);
@@ -1202,6 +1215,17 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
         if (s2 == LB_OK) e.ms = ms;
         return s2;
     };
+    // The handle's own and the default shape are candidates too.  The latter's tiles may
+    // be lower than the candidates' eight rows (one row a tile: 128 x 100 BF16 7.3 us per
+    // step, 19.6 with eight): it is then timed beside the fastest of them, below.
+    default_shape(h);
+    TuneEntry dflt;
+    dflt.bx = h->bx; dflt.ly = h->ly; dflt.dflt = 1;
+    for (TuneEntry e : {TuneEntry{bx0, ly0, grid0}, TuneEntry{dflt.bx, dflt.ly}})
+        if (st == LB_OK && e.ly >= 8) {
+            st = time_entry(e, steps);
+            if (st == LB_OK) cands.push_back(e);
+        }
     for (int bx : {64, 128, 256, 512}) {
         if (st != LB_OK) break;
         if (!bx_supported(h->storage, bx) || (bx > 64 && bx / 2 >= maxnx)) continue;
@@ -1236,6 +1260,7 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
             std::vector<int> heights = {0};
             for (int c : FUSED_HEIGHTS)
                 if (c <= 300) heights.push_back(c);
+            if (fu0 == 2 && ly20 && (fnw0 == 0 || fnw0 == lanes / 64)) heights.push_back(ly20);   // the handle's own
             for (int ly2 : heights) {
                 if (st != LB_OK) break;
                 if (ly2 && ly2 >= maxny) continue;
@@ -1249,16 +1274,29 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
     TuneEntry best;
     if (st == LB_OK && !cands.empty()) {
         std::stable_sort(cands.begin(), cands.end(), [](const TuneEntry& x, const TuneEntry& y) { return x.ms < y.ms; });
-        const size_t nf = std::min<size_t>(cands.size(), 4);
-        for (size_t i = 0; i < nf && st == LB_OK; ++i) {
-            TuneEntry e = cands[i];
+        auto again = [&](TuneEntry& e, int runs, int n) {
             double m = 1e300;
-            for (int r = 0; r < 2 && st == LB_OK; ++r) {
-                st = time_entry(e, 4 * steps);
+            for (int r = 0; r < runs && st == LB_OK; ++r) {
+                st = time_entry(e, n);
                 m = std::min(m, e.ms);
             }
             e.ms = m;
+        };
+        const size_t nf = std::min<size_t>(cands.size(), 4);
+        for (size_t i = 0; i < nf && st == LB_OK; ++i) {
+            TuneEntry e = cands[i];
+            again(e, 2, 4 * steps);
             if (st == LB_OK && (!best.bx || e.ms < best.ms)) best = e;
+        }
+        // the default shape instead, if it is faster by more than such timings scatter
+        if (st == LB_OK && dflt.ly < 8) {
+            const int n = std::max(4 * steps, 64);
+            again(best, 4, n);
+            again(dflt, 4, n);
+            if (st == LB_OK && dflt.ms < 0.95 * best.ms) {
+                best.dflt = 1;
+                best.ms = dflt.ms;
+            }
         }
     }
     h->fusion = 1;
@@ -1283,13 +1321,14 @@ lb_status autotune(lbb_handle* h, const char* cache_path, int steps, bool batch,
         (void)set_launch(h, bx0, ly0, grid0);
         return st;
     }
-    st = set_launch(h, best.bx, best.ly, best.grid);
+    st = apply_shape(h, best);
     if (st != LB_OK) return st;
-    if (best.fusion == 2) {
+    const bool fuse = best.fusion == 2 && !best.dflt;
+    if (fuse) {
         st = set_fusion_tile(h, best.fw);
         if (st != LB_OK) return st;
     }
-    st = set_fusion(h, best.fusion, best.ly2);
+    st = set_fusion(h, fuse ? 2 : 1, fuse ? best.ly2 : 0);
     if (st != LB_OK) return st;
     if (best_out) *best_out = best;
     if (cache_path) {

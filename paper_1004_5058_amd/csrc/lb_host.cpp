@@ -129,6 +129,7 @@ bool parse_line(const std::string& line, std::pair<std::string, TuneEntry>* out)
     if (get_int(body, "ly2", 0, 1 << 20, &e.ly2) < 0) return false;
     if (get_int(body, "fw", 0, 256, &e.fw) < 0) return false;
     if (e.fw != 0 && e.fw != 128 && e.fw != 192 && e.fw != 256) return false;
+    if (get_int(body, "default", 0, 1, &e.dflt) < 0) return false;
     if (get_double(body, "ms", &e.ms) < 0) return false;
     out->first = key;
     out->second = e;
@@ -222,8 +223,9 @@ std::string format_cache(const TuneCache& ents)
         char buf[256];
         const TuneEntry& e = ents[i].second;
         snprintf(buf, sizeof buf,
-                 "{\"bx\": %d, \"ly\": %d, \"grid\": %d, \"fusion\": %d, \"ly2\": %d, \"fw\": %d, \"ms\": %.6f}%s\n",
-                 e.bx, e.ly, e.grid, e.fusion, e.ly2, e.fw, e.ms, i + 1 < ents.size() ? "," : "");
+                 "{\"bx\": %d, \"ly\": %d, \"grid\": %d, \"fusion\": %d, \"ly2\": %d, \"fw\": %d, %s\"ms\": %.6f}%s\n",
+                 e.bx, e.ly, e.grid, e.fusion, e.ly2, e.fw, e.dflt ? "\"default\": 1, " : "", e.ms,
+                 i + 1 < ents.size() ? "," : "");
         s += "\"" + ents[i].first + "\": " + buf;
     }
     s += "}\n";

@@ -70,7 +70,8 @@ struct TuneEntry {
     int bx = 0, ly = 0, grid = 0;
     int fusion = 1, ly2 = 0;   // time steps per pass and fused tile height (0: automatic)
     int fw = 0;                // fused kernel's lanes per step: 128, 192, 256 (0: automatic)
-    double ms = 0;
+    int dflt = 0;              // 1: single steps in the default shape were faster than this one
+    double ms = 0;             // of what is applied
 };
 using TuneCache = std::vector<std::pair<std::string, TuneEntry>>;
 
@@ -79,8 +80,9 @@ using TuneCache = std::vector<std::pair<std::string, TuneEntry>>;
 // Lines that are not of that form, keys with a quote or control character,
 // and entries whose numbers are missing, malformed or out of range (bx not in
 // {64, 128, 256, 512}, negative ly / grid / ly2, fusion not 1 or 2, fw not in
-// {0, 128, 192, 256}, ms not finite) are skipped; an entry without "fusion"
-// runs one step per pass, one without "fw" the automatic fused width.
+// {0, 128, 192, 256}, "default" not 0 or 1, ms not finite) are skipped; an entry
+// without "fusion" runs one step per pass, one without "fw" the automatic fused
+// width, one with "default": 1 single steps in the default launch shape.
 TuneCache parse_cache(const char* text, size_t len);
 // Reads and parses a cache file (missing or unreadable: empty).
 TuneCache read_cache(const char* path);

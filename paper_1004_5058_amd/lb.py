@@ -329,7 +329,8 @@ class Lattice:
     def autotune(self, cache_path=None, steps=20):
         """Pick the fastest launch shape, and for FP32 and 16-bit storage the
         steps per pass and fused block width (state preserved); returns
-        (bx, ly, ms per step)."""
+        (bx, ly, ms per step).  Small lattices may keep the default shape where
+        that is faster: launch() tells what is in effect."""
         bx, ly, ms = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_double()
         path = cache_path.encode() if cache_path else None
         _check(_lib.lb_autotune(self._h, path, int(steps), ctypes.byref(bx), ctypes.byref(ly), ctypes.byref(ms)))
