@@ -243,7 +243,9 @@ lb_status lb_load(lb_handle* h, const void* buf, size_t bytes);
  * effect.  Restores the simulation state exactly (populations, accumulators, step
  * count).  cache_path (may be NULL): JSON file of {key: {bx, ly, grid,
  * fusion, ly2, fw, [default,] ms}}, key "<gfx arch>/<storage>/<nx>x<ny>" (batches:
- * "batch<n>_<sites>"); a cached entry is applied without timing (its fusion
+ * "batch<n>_<sites>"), for FP32 and FP64 lattices off tau = 1 with "/any_tau"
+ * behind it, for batches of both kinds "/mixed_tau" (they run other kernels); a
+ * cached entry is applied without timing (its fusion
  * only where admitted; entries without it mean one step per pass, without fw
  * the automatic width), a new result is added.  Synchronises.  Allocates a
  * temporary device copy of the state while timing. */

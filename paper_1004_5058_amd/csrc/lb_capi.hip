@@ -1070,7 +1070,7 @@ lb_status time_steps(lbb_handle* h, int32_t n, double* ms)
 // lattices, keeps the fastest and leaves the simulation state exactly as it
 // was (populations, accumulators and counters are copied aside on the device
 // and restored).  Results are cached in a small JSON file keyed by
-// "<arch>/<storage>/<lattice shape>".
+// "<arch>/<storage>/<lattice shape>[/<kernels>]".
 
 using lbh::TuneEntry;
 
@@ -1103,7 +1103,10 @@ std::string tune_key(const lbb_handle* h)
         snprintf(buf, sizeof buf, "%s/%s/batch%zu_%lld", arch_name().c_str(), storage_name(h->storage),
                  h->lats.size(), sites);
     }
-    return buf;
+    // FP32 and FP64 run other kernels at tau = 1 than off it, with other best shapes
+    std::string key = buf;
+    if (h->any_general && (h->storage == LB_F32 || h->storage == LB_F64)) key += h->any_unit ? "/mixed_tau" : "/any_tau";
+    return key;
 }
 
 lb_status write_cache(const char* path, const lbh::TuneCache& ents)
