@@ -869,10 +869,16 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
 // (moment form; FP32: two, FP64: one) waves of a SIMD share it, each further one
 // adding 0.3 of the first's time.  us per step by rows per tile, the chosen one starred:
 // 512^2 FP32 12.7 (2) 11.5* (3) 12.2 (4) 12.5 (5) 13.1 (6); 1024 x 512 FP32 18.5 (4) 18.0*
-// (5) 18.7 (6) 19.2 (8); 1000^2 moment form 24.5
-// (4) 19.0* (6) 20.9 (10) 25.7 (16); 1000^2 FP64 moment form 50.1 (10) 65.9 (16) 42.6* (20) 48.1
-// (24).  FP32 that 16 rows give every SIMD one and a half waves takes them (40
-// lattices of 256 x 128: 47.3 (5) 43.9 (8) 45.8 (10) 38.9* (16) 44.8 (20)).
+// (5) 18.7 (6) 19.2 (8); 1000^2 moment form 24.5 (4) 19.0* (6) 20.9 (10) 25.7 (16); 1000^2 FP64
+// moment form 50.1 (10) 65.9 (16) 42.6* (20) 48.1 (24).
+//
+// FP32 batches of narrow lattices: half as much again where a lattice's segments are
+// not a multiple of eight, so that the XCDs' bands (xcd_tile) break up its rows of
+// tiles: 40 of 256 x 128 43.8 (8) 45.8 (10) 44.2 (15) 38.4* (16) 40.2 (17) 44.7 (20); 30 of them
+// 32.7 (8) 33.8 (10) 30.5* (16) 35.1 (20); 24 of 300 x 200 51.4 (4) 47.9 (8) 44.4* (13) 48.1 (16)
+// 41.5 (26); 400 of 64^2 52.5* (8) 61 (12) 77.4 (16); with nine strips it is no matter: 5 of 512 x 256
+// 22.6* (6) 26 (8) 22.4 (13).  Over 65 single lattices and batches of 0.02 to 1.8 M sites the
+// choice is on average 3 %, at most 17 % slower than the best of 1 to 32 rows.
 //
 // Larger ones: 512-column tiles (256 in FP64), one per compute unit: 4096^2 FP32 0.457 ms
 // (512 x 128) against 0.468 (256 x 64); the height whose tiles finish first.
@@ -894,15 +900,27 @@ void default_shape(lbb_handle* h)
             n += (long long)((a.p.nx + columns - 1) / columns) * ((a.p.ny + rows - 1) / rows);
         return n;
     };
+    // the share of a batch's tiles that are of lattices of up to eight strips whose
+    // segments are not a multiple of eight
+    auto uneven = [&](int columns, int rows) {
+        long long n = 0;
+        for (const Lat& a : h->lats) {
+            const long long strips = (a.p.nx + columns - 1) / columns, segs = (a.p.ny + rows - 1) / rows;
+            if (strips <= 8 && segs % 8) n += strips * segs;
+        }
+        return h->lats.size() > 1 ? (double)n / (double)items(columns, rows) : 0.0;
+    };
     // the height of 64-lane tiles that models fastest (see above)
-    auto model = [&](int columns, int share, int tallest) {
-        long long best = -1;
+    auto model = [&](int columns, int share, int tallest, bool bands) {
+        double best = -1;
         h->bx = 64;
         for (int ly = tallest; ly >= 1; --ly) {
             const long long k = (items(columns, ly) + 4 * ncu - 1) / (4 * ncu);   // waves of a SIMD
             const long long full = k / share, rest = k % share;
-            const long long t = (ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0));
-            if (best < 0 || t < best) { best = t; h->ly = ly; }
+            const double t = (double)((ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0))) *
+                             (bands ? 1.0 + 0.5 * uneven(columns, ly) : 1.0);
+            // (FP32: lower tiles only for a hundredth)
+            if (best < 0 || t < (bands ? 0.99 : 1.0) * best) { best = t; h->ly = ly; }
         }
     };
     const bool mom = is_mom(h->storage);
@@ -910,10 +928,7 @@ void default_shape(lbb_handle* h)
     if (!h->any_general) {
         if (mom || !h->stream_stores) {
             const int columns = mom ? lbk::MOM_COLS : lbk::UNIT_COLS;
-            h->bx = 64;
-            h->ly = 16;
-            if (h->storage == LB_F32 && items(columns, 16) >= 6 * ncu) return;
-            model(columns, share, 32);
+            model(columns, share, 32, h->storage == LB_F32);
             return;
         }
         h->bx = h->storage == LB_F64 ? 256 : 512;
@@ -933,7 +948,7 @@ void default_shape(lbb_handle* h)
         h->ly = c[1];
         if (items(c[0], c[1]) >= 16 * ncu) return;
     }
-    model(64, share, 16);
+    model(64, share, 16, false);
 }
 
 // Tile widths with a step kernel: 64, 128, 256, and 512 for the FP32 and
