@@ -240,8 +240,7 @@ void fill_desc(const Lat& a, lbk::LatDesc& d)
     d.fomega = (float)d.omega;
     d.frho0 = (float)d.rho0;
     d.finv_rho0 = (float)d.inv_rho0;
-    for (int s = 0; s < 2; ++s)
-    {
+    for (int s = 0; s < 2; ++s) {
         for (int k = 0; k < 5; ++k) d.fks[s][k] = (float)d.ks[s][k];
         for (int k = 0; k < 3; ++k) d.fkd[s][k] = (float)d.kd[s][k];
     }
@@ -249,7 +248,6 @@ void fill_desc(const Lat& a, lbk::LatDesc& d)
     d.fkx[1] = (float)d.kx[1];
     d.fu_top = (float)d.u_top;
     d.fu_bot = (float)d.u_bot;
-    d.fshift = std::exp2((float)std::lround(std::log2(a.p.rho0 / 13)));
     d.flu_top = (float)(d.u_top - (double)d.fu_top);
     d.flu_bot = (float)(d.u_bot - (double)d.fu_bot);
 }
@@ -958,13 +956,15 @@ bool bx_supported(int storage, int bx)
     return bx == 64 || bx == 128 || bx == 256 || (bx == 512 && storage >= 1 && storage <= 3);
 }
 
-// LDS one step block needs for shape (bx, ly) on this batch, and whether the
-// current device grants it.
+// LDS one step block needs for shape (bx, ly) on this batch (the more of the kernels
+// it runs; 0: no such kernel), and whether the current device grants it.
 size_t shape_lds(const lbb_handle* h, int bx, int ly)
 {
     int maxny = 1;
     for (const Lat& a : h->lats) maxny = std::max(maxny, a.p.ny);
-    return lbk::step_lds_bytes(h->storage, bx, std::min(std::min(ly, maxny), 256));
+    const size_t general = h->any_general ? lbk::step_lds_bytes(h->storage, bx, std::min(std::min(ly, maxny), 256)) : 1;
+    const size_t unit = h->any_unit ? lbk::step_unit_lds_bytes(h->storage, bx) : 1;   // (whatever the height)
+    return general && unit ? std::max(general, unit) : 0;
 }
 int device_lds_limit()
 {
@@ -976,7 +976,6 @@ int device_lds_limit()
 }
 bool shape_fits(const lbb_handle* h, int bx, int ly)
 {
-    if (!h->any_general) return true;   // the tau = 1 and moment kernels use no LDS
     const size_t need = shape_lds(h, bx, ly);
     return need > 0 && need <= (size_t)device_lds_limit();
 }

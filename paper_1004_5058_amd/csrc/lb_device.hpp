@@ -21,7 +21,8 @@ struct LatDesc {
     int item_begin;        // first global work item of this lattice
     int nitems;            // nstrip * nseg
     int nstrip, nseg, ly;  // tiles: strips of bx columns, segments of ly rows
-    int ngroups;           // ceil(nx / 64) (moment form: ceil(nx / 60))
+    int ngroups;           // the single steps' partial sums, a row per 64 columns (FP64 and moment form: per
+                           // strip of one wave, lb_unit.hip)
     int ngroups2;          // partial sums of the fused two-step kernel, 2 steps x nstrip2 x waves per step
                            // (rows reserved for its widest layout; 0: no fused kernel for the storage)
     // Tiles of the fused two-step kernel: strips of fuse2_tw columns, nseg2
@@ -45,7 +46,6 @@ struct LatDesc {
     float fkd[2][3];
     float fkx[2];
     float fu_top, fu_bot;
-    float fshift;             // a power of two near rho_0 / 13, a species' sum of three populations (lb_unit.hip)
     float flu_top, flu_bot;   // what FP32 leaves of u_top, u_bot
     float frref[2], fpsiref[2], fepsi[2];
 };

@@ -32,6 +32,8 @@ hipError_t launch_step2_unit(int storage, int nw, char* base, const LatDesc* des
                              int grid, hipStream_t s);
 // (first: the step starts from the initial state: it reads the local equilibria
 // in place instead of pulling from neighbours.)
+// LDS bytes of one single-step block of bx columns (the moment form's storages too).
+size_t step_unit_lds_bytes(int storage, int bx);
 // LDS bytes of one fused block, and the blocks the device keeps on one compute unit.
 size_t step2_unit_lds_bytes(int storage, int nw);
 int step2_unit_blocks_per_cu(int storage, int nw);

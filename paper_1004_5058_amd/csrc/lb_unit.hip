@@ -1227,6 +1227,30 @@ hipError_t launch_step2_unit(int storage, int nw, char* base, const LatDesc* des
     return hipErrorInvalidValue;
 }
 
+size_t step_unit_lds_bytes(int storage, int bx)
+{
+    auto of = [](auto kernel) -> size_t {
+        hipFuncAttributes fa;
+        return hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(kernel)) == hipSuccess ? fa.sharedSizeBytes : 0;
+    };
+    switch (storage * 1000 + bx) {
+    case 64: return of(k_step_unit<StF64>);
+    case 128: return of(k_step_unit_wide<128, StF64, 0>);
+    case 256: return of(k_step_unit_wide<256, StF64, 0>);
+    case 1064: return of(k_step_unit<StF32>);
+    case 1128: return of(k_step_unit_wide<128, StF32, 0>);
+    case 1256: return of(k_step_unit_wide<256, StF32, 0>);
+    case 1512: return of(k_step_unit_wide<512, StF32, 0>);
+    case 4064: return of(k_step_mom<64, MomF32>);
+    case 4128: return of(k_step_mom<128, MomF32>);
+    case 4256: return of(k_step_mom<256, MomF32>);
+    case 5064: return of(k_step_mom<64, MomF64>);
+    case 5128: return of(k_step_mom<128, MomF64>);
+    case 5256: return of(k_step_mom<256, MomF64>);
+    default: return 0;
+    }
+}
+
 size_t step2_unit_lds_bytes(int storage, int nw)
 {
     auto run = [](auto kernel, int) -> size_t {
