@@ -270,10 +270,12 @@ struct lbb_handle {
     size_t bytes = 0;
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;   // private stream used only to record graphs
+    hipStream_t branch = nullptr;    // the same, for the second branch of a batch of both kinds
+    hipEvent_t fork = nullptr, join = nullptr;
     int cur = 0;                     // buffer holding f(t)
     int64_t t = 0, nsamples = 0;
     int bx = 256, ly = 64, grid = 0; // grid 0: one block per tile
-    int ntot = 0;
+    int ntot[2] = {0, 0};            // work items of the general kernels' and of tau = 1's lattices
     int ly_max = 1;                  // largest rows-per-tile over the lattices
     int graph_steps = 32;
     int fusion = 1;                  // time steps per step-kernel pass: 1, or 2 (k_step2)
@@ -281,7 +283,7 @@ struct lbb_handle {
     int ly2_eff = 0;                 // rows per fused tile in effect (the automatic choice resolved)
     int fnw = 0;                     // waves per step of the fused kernel as set (0: automatic)
     int fnw_eff = 2;                 // the same in effect
-    int ntot2 = 0;
+    int ntot2[2] = {0, 0};           // the same of the fused kernels
     hipGraphExec_t exec[2] = {nullptr, nullptr};   // graph starting from buffer 0 / 1
     int watchdog = 0;
     int flag_host = 0;
@@ -291,7 +293,7 @@ struct lbb_handle {
     lbk::LatDesc* d_desc() { return (lbk::LatDesc*)(base + lay.off_desc); }
     int32_t* d_tiles() { return (int32_t*)(base + lay.off_tiles); }
     int32_t* d_tiles2() { return (int32_t*)(base + lay.off_tiles2); }
-    std::vector<int32_t> tiles;      // host copy of the item -> lattice table
+    std::vector<int32_t> tiles;      // host copy of the item -> lattice table, lattices at tau = 1 first
     std::vector<int32_t> tiles2;     // the same for the fused two-step tiles
 };
 
@@ -335,14 +337,16 @@ std::vector<int> fused_order(const lbb_handle* h, int ly2)
 // rows split into fused_nseg near-equal segments and handed out tallest first, as
 // the kernels do), scheduled greedily on `slots` concurrent blocks; a tile of h rows
 // costs h + extra ticks.  The blocks go to the eight XCDs in turn (xcd_tile): the
-// first takes the most tiles, and its schedule is the answer.
-long long makespan(const lbb_handle* h, bool fused, int columns, int rows, int slots, int extra)
+// first takes the most tiles, and its schedule is the answer.  Of the lattices of one
+// kind (LatDesc::unit), which are one launch.
+long long makespan(const lbb_handle* h, int unit, bool fused, int columns, int rows, int slots, int extra)
 {
     std::priority_queue<long long, std::vector<long long>, std::greater<long long>> free_at;
     for (int c = 0; c < std::max(1, slots / 8); ++c) free_at.push(0);
     long long end = 0;
     int rot = 0;
     for (int k : fused_order(h, fused ? rows : INT32_MAX)) {
+        if (h->descs[k].unit != unit) continue;
         const Lat& a = h->lats[k];
         const int strips = (a.p.nx + columns - 1) / columns;
         const int nseg = fused ? lbh::fused_nseg(a.p.ny, rows) : (a.p.ny + rows - 1) / rows;
@@ -359,24 +363,6 @@ long long makespan(const lbb_handle* h, bool fused, int columns, int rows, int s
     return end;
 }
 
-// The same for the fused tiles: the overlap rows of the two steps take 8 ticks, at
-// tau = 1 (whose halves stage one row per tick from the first) 12.
-long long fused_makespan(const lbb_handle* h, int ly2, int slots)
-{
-    return makespan(h, true, lbk::fuse2_tw(h->storage, h->fnw_eff), ly2, slots, h->any_general ? 8 : 12);
-}
-
-// How many fused blocks of nw waves of output columns the device runs on one
-// compute unit (a batch of both kinds runs two launches per pass; the fewer
-// blocks count).
-int fused_blocks_per_cu(const lbb_handle* h, int nw)
-{
-    int n = INT32_MAX;
-    if (h->any_unit) n = std::min(n, lbk::step2_unit_blocks_per_cu(h->storage, nw));
-    if (h->any_general) n = std::min(n, lbk::step2_blocks_per_cu(h->storage, nw));
-    return n;
-}
-
 int device_cus()
 {
     int dev = 0, ncu = 256;
@@ -384,6 +370,34 @@ int device_cus()
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
         ncu = prop.multiProcessorCount;
     return ncu;
+}
+
+// How many fused blocks of nw waves of output columns the device runs on one compute
+// unit, of the lattices of one kind and (the fewer) of the batch's.
+int fused_blocks_per_cu(const lbb_handle* h, int unit, int nw)
+{
+    return unit ? lbk::step2_unit_blocks_per_cu(h->storage, nw) : lbk::step2_blocks_per_cu(h->storage, nw);
+}
+int fused_blocks_per_cu(const lbb_handle* h, int nw)
+{
+    int n = INT32_MAX;
+    for (int unit : {0, 1})
+        if (unit ? h->any_unit : h->any_general) n = std::min(n, fused_blocks_per_cu(h, unit, nw));
+    return n;
+}
+
+// The same for the fused tiles: the overlap rows of the two steps take 8 ticks, at
+// tau = 1 (whose halves stage one row per tick from the first) 12.  A batch of both
+// kinds as if its launches came one after the other.
+long long fused_makespan(const lbb_handle* h, int ly2)
+{
+    const int tw = lbk::fuse2_tw(h->storage, h->fnw_eff);
+    long long t = 0;
+    for (int unit : {0, 1})
+        if (unit ? h->any_unit : h->any_general)
+            t += makespan(h, unit, true, tw, ly2, device_cus() * std::max(1, fused_blocks_per_cu(h, unit, h->fnw_eff)),
+                          unit ? 12 : 8);
+    return t;
 }
 
 // Fused tile heights tried by the automatic choice and the tuner: odd
@@ -414,7 +428,7 @@ int auto_ly2(const lbb_handle* h)
         for (const Lat& a : h->lats)
             tiles += (long long)((a.p.nx + tw - 1) / tw) * lbh::fused_nseg(a.p.ny, c);
         if (c < maxny && tiles > 16LL * slots) break;   // shorter heights only add tiles
-        const long long t = fused_makespan(h, c, slots);
+        const long long t = fused_makespan(h, c);
         if (best_t < 0 || t < best_t) { best_t = t; best = c; }
     }
     return best;
@@ -430,16 +444,19 @@ int auto_fnw(const lbb_handle* h)
 {
     int best = 2, best_w = -1;
     if (!fusion_storage(h->storage)) return best;
-    if (!h->any_general) {
-        // tau = 1: the least strips x rows, weighted by what a row of a strip of each
-        // width costs (4096^2 FP32: 0.317, 0.263 and 0.271 ms per step at 128, 192 and 256
-        // lanes, times the strip's columns)
-        static const int c[5] = {0, 0, 39, 48, 67};
+    if (h->any_unit) {
+        // FP32 at tau = 1: the least strips x rows, weighted by what a row of a strip of
+        // each width costs (4096^2: 0.371, 0.267 and 0.294 ms per step at 128, 192 and 256
+        // lanes, times the strip's columns; off tau = 1, in a batch of both, 0.294, 0.377, 0.288)
+        static const int c[2][5] = {{0, 0, 36, 69, 71}, {0, 0, 45, 49, 72}};
         long long best_t = -1;
         for (int nw : {2, 3, 4}) {
             const int tw = lbk::fuse2_tw(h->storage, nw);
             long long t = 0;
-            for (const Lat& a : h->lats) t += (long long)((a.p.nx + tw - 1) / tw) * a.p.ny * c[nw];
+            for (size_t k = 0; k < h->lats.size(); ++k) {
+                const lb_params& p = h->lats[k].p;
+                t += (long long)((p.nx + tw - 1) / tw) * p.ny * c[h->descs[k].unit][nw];
+            }
             if (best_t < 0 || t < best_t) { best_t = t; best = nw; }
         }
         return best;
@@ -455,27 +472,31 @@ int auto_fnw(const lbb_handle* h)
 // item -> lattice table the step kernel reads.
 lb_status decompose(lbb_handle* h)
 {
-    int item = 0;
     h->ly_max = 1;
     h->tiles.clear();
-    for (size_t k = 0; k < h->lats.size(); ++k) {
-        const Lat& a = h->lats[k];
-        lbk::LatDesc& d = h->descs[k];
-        // columns of a tile: bx, but for waves that work on their own (the moment form,
-        // 64-column tiles at tau = 1)
-        const int wt = is_mom(h->storage) ? h->bx / 64 * lbk::MOM_COLS
-                                          : (d.unit && h->bx == 64 ? lbk::UNIT_COLS : h->bx);
-        d.nstrip = (a.p.nx + wt - 1) / wt;
-        d.ly = std::min(std::min(h->ly, a.p.ny), 256);   // the kernel's halo buffer holds 256 rows
-        d.nseg = (a.p.ny + d.ly - 1) / d.ly;
-        h->ly_max = std::max(h->ly_max, d.ly);
-        d.nitems = d.nstrip * d.nseg;
-        d.item_begin = item;
-        item += d.nitems;
-        h->tiles.resize(item, (int32_t)k);
+    for (int unit : {1, 0}) {
+        int item = 0;
+        for (size_t k = 0; k < h->lats.size(); ++k) {
+            const Lat& a = h->lats[k];
+            lbk::LatDesc& d = h->descs[k];
+            if (d.unit != unit) continue;
+            // columns of a tile: bx, but for waves that work on their own (the moment form,
+            // 64-column tiles at tau = 1)
+            const int wt = is_mom(h->storage) ? h->bx / 64 * lbk::MOM_COLS
+                                              : (d.unit && h->bx == 64 ? lbk::UNIT_COLS : h->bx);
+            d.nstrip = (a.p.nx + wt - 1) / wt;
+            d.ly = std::min(std::min(h->ly, a.p.ny), 256);   // the kernel's halo buffer holds 256 rows
+            d.nseg = (a.p.ny + d.ly - 1) / d.ly;
+            h->ly_max = std::max(h->ly_max, d.ly);
+            d.nitems = d.nstrip * d.nseg;
+            d.item_begin = item;
+            item += d.nitems;
+            h->tiles.insert(h->tiles.end(), d.nitems, (int32_t)k);
+        }
+        h->ntot[unit] = item;
     }
-    if (item > h->lay.max_items) return fail(LB_EINVAL, "launch shape gives more work items than planned");
-    h->ntot = item;
+    if ((long long)h->tiles.size() > h->lay.max_items)
+        return fail(LB_EINVAL, "launch shape gives more work items than planned");
     // Fused two-step tiles: fuse2_tw columns x ly2 rows.  ly2 = 0 picks the height
     // whose tiles, handed to the compute units in table order (each takes the
     // next tile when it finishes one), finish first; a tile of h rows costs
@@ -485,21 +506,25 @@ lb_status decompose(lbb_handle* h)
     if (ly2 <= 0) ly2 = auto_ly2(h);
     h->ly2_eff = ly2;
     const int tw = lbk::fuse2_tw(h->storage, h->fnw_eff);
-    int item2 = 0;
     h->tiles2.clear();
-    for (int k : fused_order(h, ly2)) {
-        const Lat& a = h->lats[k];
-        lbk::LatDesc& d = h->descs[k];
-        d.nstrip2 = (a.p.nx + tw - 1) / tw;
-        d.nseg2 = lbh::fused_nseg(a.p.ny, ly2);
-        d.ly2 = (a.p.ny + d.nseg2 - 1) / d.nseg2;   // the tallest segment
-        d.nitems2 = d.nstrip2 * d.nseg2;
-        d.item_begin2 = item2;
-        item2 += d.nitems2;
-        h->tiles2.resize(item2, (int32_t)k);
+    for (int unit : {1, 0}) {
+        int item2 = 0;
+        for (int k : fused_order(h, ly2)) {
+            const Lat& a = h->lats[k];
+            lbk::LatDesc& d = h->descs[k];
+            if (d.unit != unit) continue;
+            d.nstrip2 = (a.p.nx + tw - 1) / tw;
+            d.nseg2 = lbh::fused_nseg(a.p.ny, ly2);
+            d.ly2 = (a.p.ny + d.nseg2 - 1) / d.nseg2;   // the tallest segment
+            d.nitems2 = d.nstrip2 * d.nseg2;
+            d.item_begin2 = item2;
+            item2 += d.nitems2;
+            h->tiles2.insert(h->tiles2.end(), d.nitems2, (int32_t)k);
+        }
+        h->ntot2[unit] = item2;
     }
-    if (item2 > h->lay.max_items2) return fail(LB_EINVAL, "fused tile height gives more work items than planned");
-    h->ntot2 = item2;
+    if ((long long)h->tiles2.size() > h->lay.max_items2)
+        return fail(LB_EINVAL, "fused tile height gives more work items than planned");
     HIP_TRY(hipMemcpyAsync(h->d_desc(), h->descs.data(), sizeof(lbk::LatDesc) * h->descs.size(),
                            hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->d_tiles(), h->tiles.data(), sizeof(int32_t) * h->tiles.size(),
@@ -511,39 +536,41 @@ lb_status decompose(lbb_handle* h)
     return LB_OK;
 }
 
-int launch_grid(const lbb_handle* h)
+int launch_grid(const lbb_handle* h, int unit)
 {
-    if (h->grid > 0) return h->grid;
-    return std::max(1, h->ntot);
+    return h->grid > 0 ? std::min(h->grid, h->ntot[unit]) : h->ntot[unit];
 }
 
-lb_status launch_one(lbb_handle* h, hipStream_t s, int src, int first = 0)
+// One step; the lattices at tau = 1 on s, the others on s0.
+lb_status launch_one(lbb_handle* h, hipStream_t s, hipStream_t s0, int src, int first = 0)
 {
     hipError_t e = hipSuccess;
+    const int32_t* const tiles = h->d_tiles();
     if (is_mom(h->storage)) {
-        e = lbk::launch_step_mom(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(), h->ntot, src, first,
-                                 launch_grid(h), s);
+        e = lbk::launch_step_mom(h->storage, h->bx, h->base, h->d_desc(), tiles, h->ntot[1], src, first,
+                                 launch_grid(h, 1), s);
     } else {
         if (h->any_unit)
-            e = lbk::launch_step_unit(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(), h->ntot, src,
-                                      h->stream_stores, launch_grid(h), s);
+            e = lbk::launch_step_unit(h->storage, h->bx, h->base, h->d_desc(), tiles, h->ntot[1], src,
+                                      h->stream_stores, launch_grid(h, 1), s);
         if (e == hipSuccess && h->any_general)
-            e = lbk::launch_step(h->storage, h->bx, h->base, h->d_desc(), h->d_tiles(), h->ntot, src,
-                                 h->stream_stores, launch_grid(h), h->ly_max, s);
+            e = lbk::launch_step(h->storage, h->bx, h->base, h->d_desc(), tiles + h->ntot[1], h->ntot[0], src,
+                                 h->stream_stores, launch_grid(h, 0), h->ly_max, s0);
     }
     if (e != hipSuccess) return fail(LB_EDEVICE, "step launch failed: %s", hipGetErrorString(e));
     return LB_OK;
 }
 
 // Steps t and t+1 in one launch: reads buffer src, writes buffer src ^ 1.
-lb_status launch_two(lbb_handle* h, hipStream_t s, int src)
+lb_status launch_two(lbb_handle* h, hipStream_t s, hipStream_t s0, int src)
 {
-    const int grid = std::max(1, h->ntot2);
     hipError_t e = hipSuccess;
+    const int32_t* const tiles = h->d_tiles2();
+    const int* const n = h->ntot2;
     if (h->any_unit)
-        e = lbk::launch_step2_unit(h->storage, h->fnw_eff, h->base, h->d_desc(), h->d_tiles2(), h->ntot2, src, grid, s);
+        e = lbk::launch_step2_unit(h->storage, h->fnw_eff, h->base, h->d_desc(), tiles, n[1], src, n[1], s);
     if (e == hipSuccess && h->any_general)
-        e = lbk::launch_step2(h->storage, h->fnw_eff, h->base, h->d_desc(), h->d_tiles2(), h->ntot2, src, grid, s);
+        e = lbk::launch_step2(h->storage, h->fnw_eff, h->base, h->d_desc(), tiles + n[1], n[0], src, n[0], s0);
     if (e != hipSuccess) return fail(LB_EDEVICE, "fused step launch failed: %s", hipGetErrorString(e));
     return LB_OK;
 }
@@ -551,19 +578,39 @@ lb_status launch_two(lbb_handle* h, hipStream_t s, int src)
 lb_status build_graph(lbb_handle* h, int start)
 {
     if (!h->capture) HIP_TRY(hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking));
+    // A batch of both kinds: the lattices do not depend on each other, so the graph has a
+    // branch for either kind's launches, which share the chip: 20 of 256 x 128 FP32 in
+    // pairs 48.5 us a step one after the other, 33.9 in branches (one launch for both, of
+    // the general kernel: 42.6); six of 512 x 256 to 2048 x 1024 122, 94.6 (89.5).
+    const bool both = h->any_unit && h->any_general;
+    if (both && !h->branch) HIP_TRY(hipStreamCreateWithFlags(&h->branch, hipStreamNonBlocking));
+    if (both && !h->fork) HIP_TRY(hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
+    if (both && !h->join) HIP_TRY(hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
+    const hipStream_t s0 = both ? h->branch : h->capture;
     HIP_TRY(hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
     lb_status st = LB_OK;
+    hipError_t ec = hipSuccess;
     int src = start;
+    if (both) {
+        ec = hipEventRecord(h->fork, h->capture);
+        if (ec == hipSuccess) ec = hipStreamWaitEvent(h->branch, h->fork, 0);
+        if (ec != hipSuccess) st = fail(LB_EDEVICE, "graph branch failed: %s", hipGetErrorString(ec));
+    }
     if (h->fusion == 2) {
         for (int k = 0; k < h->graph_steps / 2 && st == LB_OK; ++k) {
-            st = launch_two(h, h->capture, src);
+            st = launch_two(h, h->capture, s0, src);
             src ^= 1;
         }
     } else {
         for (int k = 0; k < h->graph_steps && st == LB_OK; ++k) {
-            st = launch_one(h, h->capture, src);
+            st = launch_one(h, h->capture, s0, src);
             src ^= 1;
         }
+    }
+    if (both && ec == hipSuccess) {      // joined also after a failed launch: the capture has to end
+        ec = hipEventRecord(h->join, h->branch);
+        if (ec == hipSuccess) ec = hipStreamWaitEvent(h->capture, h->join, 0);
+        if (ec != hipSuccess && st == LB_OK) st = fail(LB_EDEVICE, "graph branch failed: %s", hipGetErrorString(ec));
     }
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(h->capture, &g);
@@ -591,7 +638,7 @@ lb_status steps(lbb_handle* h, int32_t n)
     if (n > 0 && first_state(h)) {
         // the moment form's first step reads the initial local equilibria in
         // place; it is launched on its own, never inside a graph
-        lb_status st = launch_one(h, h->stream, h->cur, 1);
+        lb_status st = launch_one(h, h->stream, h->stream, h->cur, 1);
         if (st != LB_OK) return st;
         h->cur ^= 1;
         h->t += 1;
@@ -635,7 +682,7 @@ lb_status steps(lbb_handle* h, int32_t n)
         }
         if (h->fusion == 2) {
             for (; chunk >= 2; chunk -= 2, n -= 2) {
-                lb_status st = launch_two(h, h->stream, h->cur);
+                lb_status st = launch_two(h, h->stream, h->stream, h->cur);
                 if (st != LB_OK) return st;
                 h->cur ^= 1;
                 h->t += 2;
@@ -643,7 +690,7 @@ lb_status steps(lbb_handle* h, int32_t n)
             }
         }
         for (int k = 0; k < chunk; ++k) {
-            lb_status st = launch_one(h, h->stream, h->cur);
+            lb_status st = launch_one(h, h->stream, h->stream, h->cur);
             if (st != LB_OK) return st;
             h->cur ^= 1;
             h->t += 1;
@@ -892,48 +939,57 @@ void default_shape(lbb_handle* h)
     int maxnx = 0;
     h->grid = 0;
     for (const Lat& a : h->lats) maxnx = std::max(maxnx, a.p.nx);
-    auto items = [&](int columns, int rows) {
+    // tiles of the lattices of one kind (of `columns`; unit: the narrower of one wave)
+    auto items = [&](int unit, int columns, int rows) {
         long long n = 0;
-        for (const Lat& a : h->lats)
-            n += (long long)((a.p.nx + columns - 1) / columns) * ((a.p.ny + rows - 1) / rows);
+        for (size_t q = 0; q < h->lats.size(); ++q) {
+            const lb_params& p = h->lats[q].p;
+            if (h->descs[q].unit == unit)
+                n += (long long)((p.nx + columns - 1) / columns) * ((p.ny + rows - 1) / rows);
+        }
         return n;
     };
+    const bool mom = is_mom(h->storage);
+    const int narrow[2] = {64, mom ? lbk::MOM_COLS : lbk::UNIT_COLS};
     // the share of a batch's tiles that are of lattices of up to eight strips whose
     // segments are not a multiple of eight
-    auto uneven = [&](int columns, int rows) {
+    auto uneven = [&](int rows) {
+        const int columns = lbk::UNIT_COLS;
         long long n = 0;
         for (const Lat& a : h->lats) {
             const long long strips = (a.p.nx + columns - 1) / columns, segs = (a.p.ny + rows - 1) / rows;
             if (strips <= 8 && segs % 8) n += strips * segs;
         }
-        return h->lats.size() > 1 ? (double)n / (double)items(columns, rows) : 0.0;
+        return h->lats.size() > 1 ? (double)n / (double)items(1, columns, rows) : 0.0;
     };
-    // the height of 64-lane tiles that models fastest (see above)
-    auto model = [&](int columns, int share, int tallest, bool bands) {
+    // the height of 64-lane tiles that models fastest (see above); a batch of both kinds
+    // as if its launches came one after the other
+    auto model = [&](int share, int tallest, bool bands) {
         double best = -1;
         h->bx = 64;
         for (int ly = tallest; ly >= 1; --ly) {
-            const long long k = (items(columns, ly) + 4 * ncu - 1) / (4 * ncu);   // waves of a SIMD
-            const long long full = k / share, rest = k % share;
-            const double t = (double)((ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0))) *
-                             (bands ? 1.0 + 0.5 * uneven(columns, ly) : 1.0);
+            double t = 0;
+            for (int unit : {0, 1}) {
+                const long long k = (items(unit, narrow[unit], ly) + 4 * ncu - 1) / (4 * ncu);   // waves of a SIMD
+                const long long full = k / share, rest = k % share;
+                t += (double)((ly + 3) * (full * (7 + 3 * share) + (rest ? 7 + 3 * rest : 0)));
+            }
+            if (bands) t *= 1.0 + 0.5 * uneven(ly);
             // (FP32: lower tiles only for a hundredth)
             if (best < 0 || t < (bands ? 0.99 : 1.0) * best) { best = t; h->ly = ly; }
         }
     };
-    const bool mom = is_mom(h->storage);
     const int share = storage_size(h->storage) == 8 ? 1 : (mom ? 3 : 2);
     if (!h->any_general) {
         if (mom || !h->stream_stores) {
-            const int columns = mom ? lbk::MOM_COLS : lbk::UNIT_COLS;
-            model(columns, share, 32, h->storage == LB_F32);
+            model(share, 32, h->storage == LB_F32);
             return;
         }
         h->bx = h->storage == LB_F64 ? 256 : 512;
         long long best = -1;
         for (int ly = 128; ly >= 16; ly -= 4) {
             // one block per compute unit at a time; a row costs a tick, a tile six more
-            const long long t = makespan(h, false, h->bx, ly, (int)ncu, 6);
+            const long long t = makespan(h, 1, false, h->bx, ly, (int)ncu, 6);
             if (best < 0 || t < best) { best = t; h->ly = ly; }
         }
         return;
@@ -944,9 +1000,9 @@ void default_shape(lbb_handle* h)
         if (c[0] > bxmax) continue;
         h->bx = c[0];
         h->ly = c[1];
-        if (items(c[0], c[1]) >= 16 * ncu) return;
+        if (items(0, c[0], c[1]) >= 16 * ncu && (!h->any_unit || items(1, c[0], c[1]) >= 16 * ncu)) return;
     }
-    model(64, share, 16, false);
+    model(share, 16, false);
 }
 
 // Tile widths with a step kernel: 64, 128, 256, and 512 for the FP32 and
@@ -1054,7 +1110,7 @@ lb_status set_fusion_tile(lbb_handle* h, int lanes)
 lb_status steps_direct_warm(lbb_handle* h, int n)
 {
     for (int k = 0; k < n; ++k) {
-        lb_status st = launch_one(h, h->stream, h->cur);
+        lb_status st = launch_one(h, h->stream, h->stream, h->cur);
         if (st != LB_OK) return st;
         h->cur ^= 1;
     }
@@ -1362,6 +1418,9 @@ void destroy_batch(lbb_handle* h)
 {
     drop_graphs(h);
     if (h->capture) (void)hipStreamDestroy(h->capture);
+    if (h->branch) (void)hipStreamDestroy(h->branch);
+    if (h->fork) (void)hipEventDestroy(h->fork);
+    if (h->join) (void)hipEventDestroy(h->join);
     delete h;
 }
 

@@ -20,7 +20,7 @@ hipError_t launch_step(int storage, int bx, char* base, const LatDesc* descs, co
 constexpr int fuse2_xo(int storage, int nw) { return (storage == 1 && nw == 2) ? 3 : 5; }
 constexpr int fuse2_tw(int storage, int nw) { return 64 * nw - 2 * fuse2_xo(storage, nw); }
 constexpr int FUSE2_NW_MIN = 2, FUSE2_NW_MAX = 4;
-// The same at tau = 1 (lb_unit.hip); each kernel steps only the lattices of its
+// The same at tau = 1 (lb_unit.hip); the items of a launch are of lattices of its
 // kind (LatDesc::unit).  A wave of the single-step kernel stores UNIT_COLS
 // columns, one of the moment form MOM_COLS.
 constexpr int UNIT_COLS = 60, MOM_COLS = 58;

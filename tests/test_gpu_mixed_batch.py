@@ -76,6 +76,48 @@ def test_mixed_batch_equals_each_lattice_alone(storage, lanes, graph):
     b.close()
 
 
+@pytest.mark.parametrize("storage,per_pass", [("f32", 1), ("f32", 2), ("f64", 1)])
+def test_every_replay_matches_direct_launches(storage, per_pass):
+    """Graphs of such a batch have a branch for either kind: every replay against direct
+    launches, with reads and a stress reset between the replays."""
+    from paper_1004_5058_amd import lb
+    graphed, direct = (lb.Batch(_specs((1.2, 1.0)), storage=storage, profile=True) for _ in range(2))
+    for b, graph in ((graphed, 6), (direct, 0)):
+        b.set_graph(graph)
+        b.set_fusion(per_pass, 12 if per_pass == 2 else 0)
+    for k in range(6):
+        for b in (graphed, direct):
+            b.step(6 if k % 2 else 13)
+        for q in range(graphed.n):
+            for x, y in zip(graphed.fields(q), direct.fields(q)):
+                np.testing.assert_array_equal(x, y, err_msg=f"replay {k}, lattice {q}")
+            np.testing.assert_array_equal(graphed.profile(q)[0], direct.profile(q)[0])
+        for x, y in zip(graphed.stress(), direct.stress()):
+            np.testing.assert_array_equal(x, y)
+        if k == 2:
+            for b in (graphed, direct):
+                b.stress_reset()
+    graphed.close()
+    direct.close()
+
+
+@pytest.mark.parametrize("n,nx,ny,per_pass", [(20, 256, 128, 1), (20, 256, 128, 2), (6, 128, 64, 1)])
+def test_mixed_batch_takes_little_longer_than_either_kind(n, nx, ny, per_pass):
+    """A step of the batch takes less than 1.5 times that of the slower kind alone (each
+    kernel over all tiles, one after the other: 1.4 to 3.3 times)."""
+    from paper_1004_5058_amd import lb
+    ra, rb = inputs.noise(nx, ny, 1)
+    times = []
+    for taus in ((1.0,), (1.2,), (1.0, 1.2)):
+        b = lb.Batch([dict(nx=nx, ny=ny, rho_a=ra, rho_b=rb, ux=None, uy=None, tau=taus[k % len(taus)]) for k in range(n)],
+                     storage="f32", profile=False)
+        b.set_fusion(per_pass)
+        b.time_steps(512)
+        times.append(min(b.time_steps(128) for _ in range(8)))
+        b.close()
+    assert times[2] <= 1.5 * max(times[:2]), times
+
+
 SHAPES = [("f32", 64, 5), ("f32", 128, 11), ("f32", 512, 16), ("f64", 64, 7), ("f64", 256, 9), ("mom32", 64, 6),
           ("mom32", 256, 13)]
 
