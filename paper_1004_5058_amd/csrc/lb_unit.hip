@@ -508,6 +508,58 @@ __device__ __forceinline__ void store_site(rsrc_t ro, const typename P::C (&e)[9
     }
 }
 
+// Row r in [0, ny): the periodic image (r itself but for a few rows).
+__device__ __forceinline__ int wrap_row(int r, int ny)
+{
+    if ((unsigned)r < (unsigned)ny) return r;
+    r %= ny;
+    return r < 0 ? r + ny : r;
+}
+
+// A thread's column in the population buffers: byte offsets of it and of its
+// neighbours, of a row and of a plane, and bytes of a species' planes.
+struct Column { unsigned vl, vc, vr, rbytes, pbytes, sbytes; };
+template <class P> __device__ __forceinline__ Column column_of(const LatDesc& d, unsigned xc)
+{
+    const unsigned xr = (xc + 1 == (unsigned)d.nx) ? 0u : xc + 1, xl = (xc == 0) ? (unsigned)(d.nx - 1) : xc - 1;
+    const unsigned es = (unsigned)sizeof(typename P::S);
+    return Column{xl * es, xc * es, xr * es, (unsigned)d.pitch * es, (unsigned)(d.plane * es),
+                  (unsigned)(9 * d.plane * (long long)es)};
+}
+
+// Row r (any row, not at or beyond a wall's if need is false) of the column.  One that is
+// not needed or lies beyond a wall is loaded through an empty resource: zeros, no access.
+template <class P>
+__device__ __forceinline__ void load_row(Raw<P>& f, const char* fin, const Column& c, int r, int ny, bool need)
+{
+    const unsigned ro = need ? (unsigned)wrap_row(r, ny) * c.rbytes : 0u, len = need ? c.sbytes : 0u;
+    f.load(make_rsrc(fin, len), make_rsrc(fin + c.sbytes, len), c.vl + ro, c.vc + ro, c.vr + ro, c.pbytes);
+}
+
+// Stores row y of the column after its collision t (slot M) into the next buffer and
+// adds the wall momentum of its links.  near: the tile has rows at or beyond a wall.
+template <int M, class P, int CP, class C>
+__device__ __forceinline__ void store_row(rsrc_t rout0, rsrc_t rout1, const Column& c, const Belt<C>& b, const Site<C>& t,
+                                          const Coef<C>& k, int y, int ny, bool near, C& mom_b, C& mom_t)
+{
+    const bool bot = near && y == 0, top = near && y == ny - 1;
+    const int ym = (y == 0) ? ny - 1 : y - 1, yp = (y == ny - 1) ? 0 : y + 1;
+    const unsigned rm = (unsigned)ym * c.rbytes, r0 = (unsigned)y * c.rbytes, rp = (unsigned)yp * c.rbytes;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        C e[9];
+        equilibria(t.r[s], s == 0 ? b.c[M].z : b.c[M].w, t.vx[s], t.vy[s], e);
+        const rsrc_t ro = s == 0 ? rout0 : rout1;
+        if (bot || top) {
+            store_site<P, CP>(ro, e, t.r[s], c.vl, c.vc, c.vr, rm, r0, rp, c.pbytes, bot, top, k.u_bot, k.u_top);
+            if (bot) mom_b += wall_momentum(e, t.r[s], true, k.u_bot);
+            if (top) mom_t += wall_momentum(e, t.r[s], false, k.u_top);
+        } else {
+            store_site<P, CP>(ro, e, t.r[s], c.vl, c.vc, c.vr, rm, r0, rp, c.pbytes, false, false, k.u_bot, k.u_top);
+        }
+    }
+}
+
 // Line profile: the sum of u_x over the wave's columns of each row it collides, in
 // FP64, added to the wave's partial of that row.  Eight rows are kept in LDS (the
 // row length makes the reads below hit each of the 64 banks once) and summed
@@ -536,14 +588,6 @@ __device__ __forceinline__ void add_profile(double* __restrict__ prof, ProfileRo
 }
 
 template <int I> using Slot = std::integral_constant<int, I>;
-
-// Row r in [0, ny): the periodic image (r itself but for a few rows).
-__device__ __forceinline__ int wrap_row(int r, int ny)
-{
-    if ((unsigned)r < (unsigned)ny) return r;
-    r %= ny;
-    return r < 0 ? r + ny : r;
-}
 
 // Runs tick(slot, i) for i = 0 .. n-1 (n >= 1), the slot i mod 5 a constant.  Leaving
 // the loop at any tick keeps what is dead after a tick out of the registers.
@@ -581,7 +625,6 @@ __global__ void __launch_bounds__(64, sizeof(typename P::S) == 8 ? 2 : 1)
 k_step_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
             int src)
 {
-    using S = typename P::S;
     using C = typename P::C;
     constexpr int DEPTH = 2;
     __shared__ ProfileRows<C> rows;
@@ -589,7 +632,6 @@ k_step_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const in
     for (int w = blockIdx.x; w < ntot; w += gridDim.x) {
         const int L = tiles[w];          // owning lattice
         const LatDesc& d = descs[L];
-        if (!d.unit) continue;
         const int lin = xcd_tile(w - d.item_begin, d.nitems);
         const int strip = lin % d.nstrip, seg = lin / d.nstrip;
         const int nx = d.nx, ny = d.ny, walls = d.walls;
@@ -599,15 +641,11 @@ k_step_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const in
         const int x = x0 - 2 + lane;
         const bool own = lane >= 2 && lane < 62 && x < nx;
         const unsigned xc = (unsigned)wrap(x);
-        const unsigned xr = (xc + 1 == (unsigned)nx) ? 0u : xc + 1, xl = (xc == 0) ? (unsigned)(nx - 1) : xc - 1;
         const Coef<C> k(d);
-        const unsigned es = (unsigned)sizeof(S);
-        const unsigned sbytes = (unsigned)(9 * d.plane * (long long)es);
+        const Column col = column_of<P>(d, xc);
         const char* fin = base + d.off_f[src];
         const char* fout = base + d.off_f[src ^ 1];
-        const rsrc_t rout0 = make_rsrc(fout, sbytes), rout1 = make_rsrc(fout + sbytes, sbytes);
-        const unsigned vc = xc * es, vr = xr * es, vl = xl * es;
-        const unsigned pbytes = (unsigned)(d.plane * es), rbytes = (unsigned)d.pitch * es;
+        const rsrc_t rout0 = make_rsrc(fout, col.sbytes), rout1 = make_rsrc(fout + col.sbytes, col.sbytes);
         double* __restrict__ stress = (double*)(base + d.off_stress);
         double* __restrict__ prof = d.off_prof >= 0 ? (double*)(base + d.off_prof) + (long long)strip * ny : nullptr;
         const double* __restrict__ body = d.off_body >= 0 ? (const double*)(base + d.off_body) : nullptr;
@@ -618,13 +656,9 @@ k_step_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const in
         const int n = y1 - y0 + 4;       // rows y0-2 .. y1+1
         // whether the tile has rows at or beyond a wall
         const bool near = walls && (y0 <= 2 || y1 >= ny - 2);
-        // a row that is not needed or lies beyond a wall is loaded through an empty
-        // resource: zeros, no access
         auto load = [&](Raw<P>& f, int i) {
             const int r = y0 - 2 + i;
-            const bool need = i < n && !(near && (unsigned)r >= (unsigned)ny);
-            const unsigned ro = need ? (unsigned)wrap_row(r, ny) * rbytes : 0u, len = need ? sbytes : 0u;
-            f.load(make_rsrc(fin, len), make_rsrc(fin + sbytes, len), vl + ro, vc + ro, vr + ro, pbytes);
+            load_row<P>(f, fin, col, r, ny, i < n && !(near && (unsigned)r >= (unsigned)ny));
         };
 #pragma unroll
         for (int i = 0; i < DEPTH; ++i) load(F[i], i);
@@ -645,22 +679,7 @@ k_step_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const in
             const Site<C> t = collide<M>(b, k, body, y);
             if (prof != nullptr) add_profile(prof, rows, own ? t.ux : (C)0, y, y0, y1);
             if (!own) return;
-            const bool bot = near && y == 0, top = near && y == ny - 1;
-            const int ym = (y == 0) ? ny - 1 : y - 1, yp = (y == ny - 1) ? 0 : y + 1;
-            const unsigned rm = (unsigned)ym * rbytes, r0 = (unsigned)y * rbytes, rp = (unsigned)yp * rbytes;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                C e[9];
-                equilibria(t.r[s], s == 0 ? b.c[M].z : b.c[M].w, t.vx[s], t.vy[s], e);
-                const rsrc_t ro = s == 0 ? rout0 : rout1;
-                if (bot || top) {
-                    store_site<P, 0>(ro, e, t.r[s], vl, vc, vr, rm, r0, rp, pbytes, bot, top, k.u_bot, k.u_top);
-                    if (bot) mom_b += wall_momentum(e, t.r[s], true, k.u_bot);
-                    if (top) mom_t += wall_momentum(e, t.r[s], false, k.u_top);
-                } else {
-                    store_site<P, 0>(ro, e, t.r[s], vl, vc, vr, rm, r0, rp, pbytes, false, false, k.u_bot, k.u_top);
-                }
-            }
+            store_row<M, P, 0>(rout0, rout1, col, b, t, k, y, ny, near, mom_b, mom_t);
         });
         if (own && walls && y0 == 0) stress[xc] += (double)mom_b;
         if (own && walls && y1 == ny) stress[nx + xc] += (double)mom_t;
@@ -692,7 +711,6 @@ k_step_unit_wide(char* __restrict__ base, const LatDesc* __restrict__ descs, con
     for (int w = blockIdx.x; w < ntot; w += gridDim.x) {
         const int L = tiles[w];          // owning lattice
         const LatDesc& d = descs[L];
-        if (!d.unit) continue;
         const int lin = xcd_tile(w - d.item_begin, d.nitems);
         const int strip = lin % d.nstrip, seg = lin / d.nstrip;
         const int nx = d.nx, ny = d.ny, walls = d.walls;
@@ -702,15 +720,11 @@ k_step_unit_wide(char* __restrict__ base, const LatDesc* __restrict__ descs, con
         const int x = x0 - 2 + entry;
         const bool own = !halo && x < nx;
         const unsigned xc = (unsigned)wrap(x);
-        const unsigned xr = (xc + 1 == (unsigned)nx) ? 0u : xc + 1, xl = (xc == 0) ? (unsigned)(nx - 1) : xc - 1;
         const Coef<C> k(d);
-        const unsigned es = (unsigned)sizeof(S);
-        const unsigned sbytes = (unsigned)(9 * d.plane * (long long)es);
+        const Column col = column_of<P>(d, xc);
         const char* fin = base + d.off_f[src];
         const char* fout = base + d.off_f[src ^ 1];
-        const rsrc_t rout0 = make_rsrc(fout, sbytes), rout1 = make_rsrc(fout + sbytes, sbytes);
-        const unsigned vc = xc * es, vr = xr * es, vl = xl * es;
-        const unsigned pbytes = (unsigned)(d.plane * es), rbytes = (unsigned)d.pitch * es;
+        const rsrc_t rout0 = make_rsrc(fout, col.sbytes), rout1 = make_rsrc(fout + col.sbytes, col.sbytes);
         double* __restrict__ stress = (double*)(base + d.off_stress);
         double* __restrict__ prof = d.off_prof >= 0 ? (double*)(base + d.off_prof) + (long long)(x0 / 64 + wave) * ny : nullptr;
         const double* __restrict__ body = d.off_body >= 0 ? (const double*)(base + d.off_body) : nullptr;
@@ -721,13 +735,9 @@ k_step_unit_wide(char* __restrict__ base, const LatDesc* __restrict__ descs, con
         const int n = y1 - y0 + 4;       // rows y0-2 .. y1+1
         // whether the tile has rows at or beyond a wall
         const bool wall = walls && (y0 <= 2 || y1 >= ny - 2);
-        // a row that is not needed or lies beyond a wall is loaded through an empty
-        // resource: zeros, no access
         auto load = [&](Raw<P>& f, int i) {
             const int r = y0 - 2 + i;
-            const bool need = i < n && !(wall && (unsigned)r >= (unsigned)ny);
-            const unsigned ro = need ? (unsigned)wrap_row(r, ny) * rbytes : 0u, len = need ? sbytes : 0u;
-            f.load(make_rsrc(fin, len), make_rsrc(fin + sbytes, len), vl + ro, vc + ro, vr + ro, pbytes);
+            load_row<P>(f, fin, col, r, ny, i < n && !(wall && (unsigned)r >= (unsigned)ny));
         };
 #pragma unroll
         for (int i = 0; i < DEPTH; ++i) load(F[i], i);
@@ -751,22 +761,7 @@ k_step_unit_wide(char* __restrict__ base, const LatDesc* __restrict__ descs, con
             const Site<C> t = collide<M>(b, k, body, y);
             if (prof != nullptr && x0 + 64 * wave < nx) add_profile(prof, rows[wave], own ? t.ux : (C)0, y, y0, y1);
             if (!own) return;
-            const bool bot = wall && y == 0, top = wall && y == ny - 1;
-            const int ym = (y == 0) ? ny - 1 : y - 1, yp = (y == ny - 1) ? 0 : y + 1;
-            const unsigned rm = (unsigned)ym * rbytes, r0 = (unsigned)y * rbytes, rp = (unsigned)yp * rbytes;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                C e[9];
-                equilibria(t.r[s], s == 0 ? b.c[M].z : b.c[M].w, t.vx[s], t.vy[s], e);
-                const rsrc_t ro = s == 0 ? rout0 : rout1;
-                if (bot || top) {
-                    store_site<P, CP>(ro, e, t.r[s], vl, vc, vr, rm, r0, rp, pbytes, bot, top, k.u_bot, k.u_top);
-                    if (bot) mom_b += wall_momentum(e, t.r[s], true, k.u_bot);
-                    if (top) mom_t += wall_momentum(e, t.r[s], false, k.u_top);
-                } else {
-                    store_site<P, CP>(ro, e, t.r[s], vl, vc, vr, rm, r0, rp, pbytes, false, false, k.u_bot, k.u_top);
-                }
-            }
+            store_row<M, P, CP>(rout0, rout1, col, b, t, k, y, ny, wall, mom_b, mom_t);
         });
         if (own && walls && y0 == 0) stress[xc] += (double)mom_b;
         if (own && walls && y1 == ny) stress[nx + xc] += (double)mom_t;
@@ -932,7 +927,6 @@ __global__ void __launch_bounds__(128 * NW, 2)
 k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
              int src)
 {
-    using S = typename P::S;
     using C = typename P::C;
     using C2 = typename V2<C>::T;
     constexpr int BW = 64 * NW, XO = 5, DEPTH = 2;
@@ -963,7 +957,6 @@ k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const i
     for (int w = blockIdx.x; w < ntot; w += gridDim.x) {
         const int L = tiles[w];          // owning lattice
         const LatDesc& d = descs[L];
-        if (!d.unit) continue;
         const int lin = xcd_tile(w - d.item_begin2, d.nitems2);
         const int strip = lin % d.nstrip2, seg = lin / d.nstrip2;
         const int nx = d.nx, ny = d.ny, walls = d.walls;
@@ -974,14 +967,10 @@ k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const i
         const int y1 = y0 + sb + (seg < sx ? 1 : 0);
         const int xm = (X - XO + j) % nx;
         const unsigned xc = (unsigned)(xm < 0 ? xm + nx : xm);
-        const unsigned xr = (xc + 1 == (unsigned)nx) ? 0u : xc + 1, xl = (xc == 0) ? (unsigned)(nx - 1) : xc - 1;
+        const Column col = column_of<P>(d, xc);
         // the columns this tile stores and whose wall momentum it counts
         const bool own = j >= XO && j < XO + TW && X + (j - XO) < nx;
         const Coef<C> k(d);
-        const unsigned es = (unsigned)sizeof(S);
-        const unsigned sbytes = (unsigned)(9 * d.plane * (long long)es);
-        const unsigned vc = xc * es, vr = xr * es, vl = xl * es;
-        const unsigned pbytes = (unsigned)(d.plane * es), rbytes = (unsigned)d.pitch * es;
         const double* __restrict__ body = d.off_body >= 0 ? (const double*)(base + d.off_body) : nullptr;
         // this wave's line-profile partials of its step (waves past PW own no column)
         double* __restrict__ prof = nullptr;
@@ -1001,9 +990,7 @@ k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const i
             flow.clear();
             auto load = [&](Raw<P>& f, int i) {
                 const int r = y0 - 5 + i;
-                const bool need = i < n + 10 && !outside(r);
-                const unsigned ro = need ? (unsigned)wrap_row(r, ny) * rbytes : 0u, len = need ? sbytes : 0u;
-                f.load(make_rsrc(fin, len), make_rsrc(fin + sbytes, len), vl + ro, vc + ro, vr + ro, pbytes);
+                load_row<P>(f, fin, col, r, ny, i < n + 10 && !outside(r));
             };
 #pragma unroll
             for (int i = 0; i < DEPTH; ++i) load(F[i], i);
@@ -1067,7 +1054,7 @@ k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const i
             mom[1][j] = mt;
         } else {
             const char* fout = base + d.off_f[src ^ 1];
-            const rsrc_t rout0 = make_rsrc(fout, sbytes), rout1 = make_rsrc(fout + sbytes, sbytes);
+            const rsrc_t rout0 = make_rsrc(fout, col.sbytes), rout1 = make_rsrc(fout + col.sbytes, col.sbytes);
             Quad<C> c2{0, 0, 0, 0};                // the row to stage next, and its momentum
             C j2x = 0, j2y = 0;
             ticks(n + 12, [&](auto slot, int i) {
@@ -1102,22 +1089,7 @@ k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const i
                 const Site<C> t = collide<M>(B, k, body, y);
                 if (prof != nullptr) add_profile(prof, rows[role * NW + wave], own ? t.ux : (C)0, y, y0, y1);
                 if (!own) return;
-                const bool bot = near && y == 0, top = near && y == ny - 1;
-                const int ym = (y == 0) ? ny - 1 : y - 1, yp = (y == ny - 1) ? 0 : y + 1;
-                const unsigned rm = (unsigned)ym * rbytes, r0 = (unsigned)y * rbytes, rp = (unsigned)yp * rbytes;
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    C e[9];
-                    equilibria(t.r[s], s == 0 ? B.c[M].z : B.c[M].w, t.vx[s], t.vy[s], e);
-                    const rsrc_t ro = s == 0 ? rout0 : rout1;
-                    if (bot || top) {
-                        store_site<P, 0>(ro, e, t.r[s], vl, vc, vr, rm, r0, rp, pbytes, bot, top, k.u_bot, k.u_top);
-                        if (bot) mb += wall_momentum(e, t.r[s], true, k.u_bot);
-                        if (top) mt += wall_momentum(e, t.r[s], false, k.u_top);
-                    } else {
-                        store_site<P, 0>(ro, e, t.r[s], vl, vc, vr, rm, r0, rp, pbytes, false, false, k.u_bot, k.u_top);
-                    }
-                }
+                store_row<M, P, 0>(rout0, rout1, col, B, t, k, y, ny, near, mb, mt);
             });
         }
         __syncthreads();
