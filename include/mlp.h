@@ -19,7 +19,9 @@
  * Conventions follow lb.h: lb_status return codes, lb_last_error() for the
  * message, caller-owned device state of mlp_state_bytes(max_rows) bytes
  * (256-byte aligned), all work on the stream given at init; functions that
- * take or return host arrays synchronise.
+ * take or return host arrays synchronise.  A handle owns, besides, pinned host
+ * memory for short inferences: 16 bytes per row up to 4096 rows of max_rows
+ * (none if the system grants none: these then copy through the device state).
  */
 #ifndef MLP_H
 #define MLP_H
@@ -39,6 +41,7 @@ typedef struct mlp_handle mlp_handle;
 
 /* Device bytes for a network that trains / infers on up to max_rows rows. */
 lb_status mlp_state_bytes(int32_t max_rows, size_t* bytes);
+/* Allocates the handle's pinned rows (about 80 us of the 260 a handle takes). */
 lb_status mlp_init(void* dev_state, size_t bytes, int32_t max_rows, void* hip_stream, mlp_handle** out);
 
 /* Host float arrays of MLP_NPARAM values.  mlp_set_params also resets Adam. */
@@ -62,6 +65,8 @@ lb_status mlp_train(mlp_handle* h, int32_t iters, float lr, float* loss);
 /* Predictions on the original scale for n <= max_rows host rows X (n, 3). */
 lb_status mlp_infer(mlp_handle* h, const float* X, int32_t n, float* y);
 
+/* Frees the handle and its pinned rows, for which the system may wait for the
+ * device; never the caller's device state. */
 lb_status mlp_destroy(mlp_handle* h);
 
 #ifdef __cplusplus
