@@ -913,8 +913,8 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
 // height that models fastest: a tile of ly rows takes ly + 3 row times, up to three
 // (moment form; FP32: two, FP64: one) waves of a SIMD share it, each further one
 // adding 0.3 of the first's time.  us per step by rows per tile, the chosen one starred:
-// 512^2 FP32 12.7 (2) 11.5* (3) 12.2 (4) 12.5 (5) 13.1 (6); 1024 x 512 FP32 18.5 (4) 18.0*
-// (5) 18.7 (6) 19.2 (8); 1000^2 moment form 24.5 (4) 19.0* (6) 20.9 (10) 25.7 (16); 1000^2 FP64
+// 512^2 FP32 13.1 (2) 11.8* (3) 13.0 (4) 12.9 (5) 13.8 (6); 1024 x 512 FP32 18.7 (4) 17.9*
+// (5) 18.9 (6) 19.3 (8); 1000^2 moment form 24.5 (4) 19.0* (6) 20.9 (10) 25.7 (16); 1000^2 FP64
 // moment form 50.1 (10) 65.9 (16) 42.6* (20) 48.1 (24).
 //
 // FP32 batches of narrow lattices: half as much again where a lattice's segments are
@@ -925,14 +925,14 @@ lb_status line_profile(lbb_handle* h, int k, double* prof)
 // 22.6* (6) 26 (8) 22.4 (13).  Over 65 single lattices and batches of 0.02 to 1.8 M sites the
 // choice is on average 3 %, at most 17 % slower than the best of 1 to 32 rows.
 //
-// Larger ones: 512-column tiles (256 in FP64), one per compute unit: 4096^2 FP32 0.457 ms
-// (512 x 128) against 0.468 (256 x 64); the height whose tiles finish first.
+// Larger ones: 512-column tiles (256 in FP64), one per compute unit: 4096^2 FP32 0.458 ms
+// (512 x 128) against 0.470 (256 x 64); the height whose tiles finish first.
 //
 // Otherwise: the widest tile and tallest segment that still give about sixteen
 // items per compute unit, or where none does 64-lane tiles of the height that models
 // fastest, as above.  us per step by rows per tile: 128 x 100 BF16 7.3* (1) 8.9 (2) 19.6 (8);
-// 519 x 376 FP32 17.4 (1) 13.2* (2) 14.3 (3) 15.3 (4) 21.0 (8); 777 x 333 FP32 16.4 (2)
-// 15.4* (3) 16.8 (4) 21.9 (8); 1000 x 700 FP64 56.9 (8) 45.6* (12) 49.7 (16).
+// 519 x 376 FP32 17.9 (1) 13.9* (2) 15.2 (3) 16.1 (4) 22.2 (8); 777 x 333 FP32 17.0 (2)
+// 16.2* (3) 17.8 (4) 23.2 (8); 1000 x 700 FP64 56.9 (8) 45.6* (12) 49.7 (16).
 void default_shape(lbb_handle* h)
 {
     const long long ncu = device_cus();

@@ -2,8 +2,8 @@
 // where the BGK collision of Eq. (1) replaces every population by the
 // equilibrium at the shifted velocity, f*_is = f^eq_i(rho_s, v_s).  FP64, FP32 and
 // the moment form run these kernels at tau = 1 (16-bit storage keeps the roundings of
-// the general ones).  Per step before and now: 4096^2 FP32 in pairs 0.286 -> 0.262 ms,
-// moment form 0.258 -> 0.194; 128^2 FP64 20 -> 8.7 us; 512^2 FP32 in pairs 19 -> 13 us, single steps 11.8.
+// the general ones).  Per step of those and of these: 4096^2 FP32 in pairs 0.286, 0.266 ms,
+// moment form 0.258, 0.194; 128^2 FP64 20, 8.6 us; 512^2 FP32 in pairs 19, 13.7, single steps 12.1.
 //
 // What tau = 1 saves.  Nothing of a row's populations is needed past its four
 // sums (the two density deviations and the momentum), so a row leaves the
@@ -691,7 +691,7 @@ k_step_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const in
 // exchange psi and rho through one LDS row per tick behind one barrier; an extra
 // wave stages the two columns beyond each side.  Large lattices run it: waves
 // on their own store 240-byte pieces of a row at different times, so a tenth
-// of the sectors reach HBM in two parts (4096^2 FP32: 0.73 against 0.47 ms).
+// of the sectors reach HBM in two parts (4096^2 FP32: 0.73 against 0.46 ms).
 template <int BX, class P, int CP>
 __global__ void __launch_bounds__(BX + 64)
 k_step_unit_wide(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
@@ -917,11 +917,12 @@ k_step_mom(char* __restrict__ base, const LatDesc* __restrict__ descs, const int
 // and one of streaming for each step, less the outermost of step t's streaming).
 //
 // What bounds it: the issue rate of a wave at few waves per SIMD, so the registers.
-// A half keeps one belt of rows and two rows of loads in 195 registers, two waves per
+// A half keeps one belt of rows and two rows of loads in 196 registers, two waves per
 // SIMD; both steps in one thread took 241 and ran twice the work in each.  Between the steps eleven sums per column cross
 // LDS instead of eighteen populations of nine rows.  It runs best at 182 columns and
-// six waves a compute unit (4096^2: 0.262 ms a step; 246 columns, eight waves: 0.274;
-// 118 columns, two blocks of four: 0.31).
+// six waves a compute unit (4096^2: 0.266 ms a step; 246 columns, eight waves: 0.294;
+// 122 columns, six waves: 0.371; two blocks of four waves and 118 columns, when psi was ten
+// instructions shorter: 0.31 against 0.262).
 template <class P, int NW, int TW, int PW>
 __global__ void __launch_bounds__(128 * NW, 2)
 k_step2_unit(char* __restrict__ base, const LatDesc* __restrict__ descs, const int* __restrict__ tiles, int ntot,
